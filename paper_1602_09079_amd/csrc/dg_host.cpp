@@ -501,6 +501,22 @@ TableLayout make_layout(int k, int prec) {
 
 hipError_t stage_occupancy(int k, int prec, int lds_bytes, int *blocks_per_cu);
 
+// x-blocks per row of cells and y rows per work item of the context's stage kernel
+static int stage_nbx(const dg_ctx *c) {
+    const int b = c->cell ? CELL_TILE : c->k3x ? K3_BLK : BLK_INNER;
+    return (c->cfg.n[0] + b - 1) / b;
+}
+// Whether the one-cell-per-lane kernel splits each tile and plane over several waves by task: where the
+// tiles of a plane are so few that a wave's own chain of dependent instructions is the launch's time
+// (stage at 16^3 split / not, us: k = 1 FP64 8.8 / 14.9, k = 2 FP32 13.5 / 30.4, FP64 19.3 / 47.9; at
+// 32^3 9.5 / 12.5 (k = 1 FP32), 28.7 / 35.8, 41 / 59; at 40^2 x 41 the k = 2 FP32 stage loses, 65 / 56).
+// The two forms round differently, so the rule looks at the plane only: a z slab takes the same one as
+// the whole mesh, and the z chunk length does not enter.
+static bool stage_split(const dg_ctx *c) {
+    return ((c->cfg.n[0] + CELL_TILE - 1) / CELL_TILE) * (long long)((c->cfg.n[1] + CELL_TILE - 1) / CELL_TILE) <= 16;
+}
+static int stage_rows(const dg_ctx *c) { return c->cell ? CELL_TILE : stage_rows_per_item(c->cfg.precision); }
+
 // ====================================================================== ABI
 
 extern "C" {
@@ -586,7 +602,8 @@ dg_status dg_init(const dg_config *cfg, void *hip_stream, dg_ctx **out) {
     // k = 3 in the FP32-storage tiers: the kernel of stage_k3.hip; k = 4: stage_k4.hip
     c->k3x = cfg->k == 3 && cfg->precision != DG_FP64;
     c->k4m = cfg->k == 4;
-    if (cfg->k >= 1) {  // k = 0 runs the finite-volume kernel, which needs no product tables
+    c->cell = (cfg->k == 1 || cfg->k == 2) && (cfg->precision == DG_FP64 || cfg->precision == DG_FP32);
+    if (cfg->k >= 1 && !c->cell) {  // the finite-volume and the one-cell-per-lane kernels need no product tables
         std::vector<char> blob;
         if (c->k4m) {
             blob = build_tables_k4(cfg->precision, s);
@@ -668,7 +685,7 @@ dg_status dg_init(const dg_config *cfg, void *hip_stream, dg_ctx **out) {
         *out = c;
         return DG_OK;
     }
-    {
+    if (!c->cell) {
         int dev0 = 0, maxlds = 0;
         if (hipGetDevice(&dev0) != hipSuccess ||
             hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev0) != hipSuccess)
@@ -695,23 +712,25 @@ dg_status dg_init(const dg_config *cfg, void *hip_stream, dg_ctx **out) {
             c->lds += K3_GHOST_BYTES;
         }
     }
-    if ((c->k3x ? set_stage_k3_attributes(cfg->precision, c->lds)
-                : set_stage_attributes(cfg->k, cfg->precision, c->lds)) != hipSuccess)
+    if (!c->cell && (c->k3x ? set_stage_k3_attributes(cfg->precision, c->lds)
+                            : set_stage_attributes(cfg->k, cfg->precision, c->lds)) != hipSuccess)
         return fail(DG_ERR_HIP);
     int dev = 0, ncu = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return fail(DG_ERR_HIP);
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return fail(DG_ERR_HIP);
-    if ((c->k3x ? stage_k3_occupancy(cfg->precision, c->lds, &per_cu)
-                : stage_occupancy(cfg->k, cfg->precision, c->lds, &per_cu)) != hipSuccess ||
+    if (c->cell && stage_cell_setup(cfg->k, cfg->precision, &per_cu) != hipSuccess) return fail(DG_ERR_HIP);
+    if ((c->cell  ? hipSuccess
+         : c->k3x ? stage_k3_occupancy(cfg->precision, c->lds, &per_cu)
+                  : stage_occupancy(cfg->k, cfg->precision, c->lds, &per_cu)) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
     // z chunk length: the resident item slots take the items in rounds, and an item costs its
     // planes plus about one plane of start-up (the -z face of its first plane, the look-ahead
     // that is not yet overlapped); pick the length (at most 32) that minimises
     // rounds x (length + 1), the longer one on ties
-    const long long nbx = c->k3x ? (cfg->n[0] + K3_BLK - 1) / K3_BLK : (cfg->n[0] + BLK_INNER - 1) / BLK_INNER;
-    const int rows = stage_rows_per_item(cfg->precision);
-    const int items_per_wg = rows == 1 ? stage_block_threads(cfg->precision) / 64 : 1;  // one item per wave or per workgroup
+    const long long nbx = stage_nbx(c);
+    const int rows = stage_rows(c);
+    const int items_per_wg = c->cell ? CELL_WAVES : rows == 1 ? stage_block_threads(cfg->precision) / 64 : 1;  // one item per wave or per workgroup
     const long long nyg = (cfg->n[1] + rows - 1) / rows;
     const long long resident = std::max(1LL, (long long)per_cu * ncu * items_per_wg);
     long long zl = 1, best = -1;
@@ -845,11 +864,20 @@ dg_status run_stage(dg_ctx *c, const void *y0, const void *yin, void *out, doubl
     s.nx = c->cfg.n[0];
     s.ny = c->cfg.n[1];
     s.nz = c->cfg.n[2];
-    s.nbx = c->k3x ? (c->cfg.n[0] + K3_BLK - 1) / K3_BLK : (c->cfg.n[0] + BLK_INNER - 1) / BLK_INNER;
+    s.nbx = stage_nbx(c);
     s.zlen = c->zlen;
     {
-        const int rows = stage_rows_per_item(c->cfg.precision);
+        const int rows = stage_rows(c);
         s.nitems = (long long)s.nbx * ((s.ny + rows - 1) / rows) * ((s.nz + c->zlen - 1) / c->zlen);
+    }
+    if (c->cell) {
+        if (stage_split(c)) {
+            s.wgw = 0;
+            s.nitems = (long long)s.nbx * ((s.ny + CELL_TILE - 1) / CELL_TILE) * s.nz;
+        } else {
+            // a mesh that cannot fill the chip with workgroups of four waves gives each wave a workgroup
+            s.wgw = s.nitems <= 1024 ? 1 : CELL_WAVES;
+        }
     }
     s.ex_off = c->ex_off;
     s.ex_off2 = c->ex_off2;
@@ -863,12 +891,17 @@ dg_status run_stage(dg_ctx *c, const void *y0, const void *yin, void *out, doubl
     s.halo_lo = c->halo_lo;
     s.halo_hi = c->halo_hi;
     s.acache = c->acache;
-    for (int i = 0; i < 3; i++) s.h[i] = c->h[i];
+    for (int i = 0; i < 3; i++) {
+        s.h[i] = c->h[i];
+        s.ih[i] = 1.0 / c->h[i];
+    }
     s.dtab = c->dtab;
     s.dcs = c->dcs;
     s.dks = c->dks;
     if (c->k3x)
         HIPCHK(c, launch_stage_k3(c->cfg.precision, s, c->grid, c->lds, c->stream));
+    else if (c->cell)
+        HIPCHK(c, launch_stage_cell(c->cfg.k, c->cfg.precision, s, c->stream));
     else if (c->k4m)
         HIPCHK(c, launch_stage_k4(c->cfg.precision, s, c->grid, c->stream));
     else
@@ -1124,13 +1157,13 @@ dg_status dg_set_forcing(dg_ctx *c, int32_t nmodes, const int32_t *nvec, const d
     }
     if (!c->fmodes) HIPCHK(c, hipMalloc(&c->fmodes, t.size() * sizeof(double)));
     if (!c->acache)
-        HIPCHK(c, hipMalloc(&c->acache, (size_t)accel_slab_elems(c->cfg.k, c->cfg.n[0]) * c->cfg.n[1] * c->cfg.n[2] *
+        HIPCHK(c, hipMalloc(&c->acache, (size_t)accel_slab_elems(c->cfg.k, c->cfg.n[0], c->cell) * c->cfg.n[1] * c->cfg.n[2] *
                                             elem_bytes(c)));
     HIPCHK(c, hipMemcpyAsync(c->fmodes, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
     GaussNodes xg{};
     double wg[5];
     gauss_rule(c->n, xg.x, wg);
-    HIPCHK(c, launch_accel_cache(c->cfg.k, c->cfg.precision, c->fmodes, nmodes, c->cfg.n[0], c->cfg.n[1], c->cfg.n[2],
+    HIPCHK(c, launch_accel_cache(c->cfg.k, c->cfg.precision, c->cell, c->fmodes, nmodes, c->cfg.n[0], c->cfg.n[1], c->cfg.n[2],
                                  c->ncells, xg, c->slab_z0, c->slab_nz > 0 ? c->slab_nz : c->cfg.n[2], c->acache,
                                  c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));

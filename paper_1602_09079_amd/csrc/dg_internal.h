@@ -146,8 +146,9 @@ struct GaussNodes {
     double x[5];
 };
 // elements of the driving acceleration cache per (z, y) row of cells: 3 components x 16 ceil(Q/16) points x nx
-inline long long accel_slab_elems(int k, int nx) {
-    if (k == 0) return 3LL * nx;  // k = 0: [component][x], the cell centre only
+// (k = 0 and the one-cell-per-lane kernel: [component][point][x], Q points)
+inline long long accel_slab_elems(int k, int nx, bool cell) {
+    if (k == 0 || cell) return 3LL * (k + 1) * (k + 1) * (k + 1) * nx;
     const int Q = (k + 1) * (k + 1) * (k + 1);
     return (long long)((Q + 15) / 16) * 16 * 3 * nx;
 }
@@ -188,7 +189,7 @@ hipError_t launch_fill_zero(unsigned long long *p, long long n, hipStream_t s);
 hipError_t launch_sum_into(const double *p, long long n, double *acc, hipStream_t s);
 hipError_t launch_reset(int k, int prec, void *y, const Leg1D &L, long long nc, int nx, double gm1, double ce,
                         double rho0, double vol, double *partials, double *acc, hipStream_t s);
-hipError_t launch_accel_cache(int k, int prec, const double *modes, int nmodes, int nx, int ny, int nz, long long nc,
+hipError_t launch_accel_cache(int k, int prec, bool cell, const double *modes, int nmodes, int nx, int ny, int nz, long long nc,
                               const GaussNodes &xg, int z0, int nzg, void *out, hipStream_t s);
 
 struct StageArgs {
@@ -204,6 +205,7 @@ struct StageArgs {
     int nx, ny, nz;
     int nbx;              // x-blocks per row
     int zlen;             // cells per z chunk swept by one wave
+    int wgw;              // one-cell-per-lane kernel: waves per workgroup, 0: tiles split by task
     long long nitems;     // work items: nbx * ceil(ny / rows per item) * ceil(nz / zlen)
     int ex_off;           // LDS byte offset of the y-face trace slots
     int ex_off2;          // LDS byte offset of the y-face flux slots (== ex_off: shared, ex_single = 1)
@@ -215,6 +217,7 @@ struct StageArgs {
     int forcing;          // 1: add the driving source
     const void *acache;   // driving acceleration at the volume points (layout of accel_load)
     double h[3];          // cell widths
+    double ih[3];         // 1 / h
     const void *corr;     // closure correction c (state layout) or nullptr: R <- R - (c - cmean on mode 0)
     const double *cmean;  // [5] mean of c's mode-0 rows per field
     int riemann;          // face flux: 0 HLLC, 1 exact Riemann solver
@@ -234,6 +237,11 @@ hipError_t set_stage_attributes(int k, int prec, int lds_bytes);
 hipError_t launch_stage_k3(int prec, const StageArgs &a, int grid, int lds_bytes, hipStream_t s);
 hipError_t set_stage_k3_attributes(int prec, int lds_bytes);
 hipError_t stage_k3_occupancy(int prec, int lds_bytes, int *per_cu);
+// the one-cell-per-lane kernel of k = 1, 2 in FP64 and FP32 (stage_cell.hip)
+constexpr int CELL_TILE = 8;  // cells per wave along x and along y
+constexpr int CELL_WAVES = 4; // waves per workgroup: consecutive tiles along x
+hipError_t launch_stage_cell(int k, int prec, const StageArgs &a, hipStream_t s);
+hipError_t stage_cell_setup(int k, int prec, int *per_cu);
 hipError_t launch_stage_k4(int prec, const StageArgs &a, int grid, hipStream_t s);
 hipError_t set_stage_k4_attributes(int prec);
 // driving factor table of the k = 3 kernel: modes [m][9] as for the cache (n as doubles, then
@@ -325,6 +333,7 @@ struct dg_ctx {
     void *acache = nullptr;        // driving acceleration at the volume points (storage type)
     // k = 3 in the FP32-storage tiers runs stage_k3_kernel (16-cell x-blocks, driving as a product)
     bool k3x = false;
+    bool cell = false; // k = 1, 2 in FP64 / FP32: the one-cell-per-lane kernel of stage_cell.hip
     bool k4m = false;  // k = 4 in FP32 / FP64: the matrix-core kernel of stage_k4.hip
     float *dtab = nullptr;         // its driving factor table, per (z, y) row
     float *dcs = nullptr;          // cos / sin of the x phases, per x

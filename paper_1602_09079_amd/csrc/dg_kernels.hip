@@ -1,6 +1,7 @@
 // HIP kernels of libdgmi.so for gfx950 (MI355X).
 //
-// The fused SSP stage kernel evaluates the modal DG operator of Bauer et al.
+// The fused SSP stage kernel of this file (k = 3 in FP64, k = 1 and 2 in the BF16-product tiers)
+// evaluates the modal DG operator of Bauer et al.
 // (arXiv 1602.09079), Sec. 2.3, on blocks of 16 cells that are consecutive in
 // x.  Every basis contraction is a dense GEMM over cells on the matrix cores:
 //
@@ -995,12 +996,9 @@ static hipError_t set_attr_t(int lds_bytes) {
 
 #define DG_DISPATCH(k, prec, CALL, ARGS)                                             \
     switch (k * 10 + prec) {                                                          \
-        case 10: return CALL<1, DG_FP64> ARGS; case 11: return CALL<1, DG_FP32> ARGS;   \
         case 12: return CALL<1, DG_BF16> ARGS; case 13: return CALL<1, DG_BF16X3> ARGS; \
-        case 20: return CALL<2, DG_FP64> ARGS; case 21: return CALL<2, DG_FP32> ARGS;   \
         case 22: return CALL<2, DG_BF16> ARGS; case 23: return CALL<2, DG_BF16X3> ARGS; \
-        case 30: return CALL<3, DG_FP64> ARGS; case 31: return CALL<3, DG_FP32> ARGS;   \
-        case 32: return CALL<3, DG_BF16> ARGS; case 33: return CALL<3, DG_BF16X3> ARGS; \
+        case 30: return CALL<3, DG_FP64> ARGS;                                        \
         default: return hipErrorInvalidValue;                                         \
     }
 
@@ -1133,12 +1131,13 @@ constexpr int ACC_THREADS = 256;
 template <int K, class S>
 __global__ __launch_bounds__(ACC_THREADS) void accel_cache_kernel(const double *__restrict__ modes, int nmodes,
                                                                   int nx, int ny, int nz, GaussNodes xg, int z0,
-                                                                  int nzg, S *__restrict__ out) {
+                                                                  int nzg, int cell, S *__restrict__ out) {
     constexpr int n = K + 1, Q = n * n * n, RT1 = (Q + 15) / 16;
     constexpr bool F64 = sizeof(S) == 8;
     __shared__ double P[MAX_FORCING_MODES][3][2];
     const long long items = (long long)ny * nz * n * n;
-    const long long aslab = K == 0 ? 3LL * nx : (long long)RT1 * 16 * 3 * nx;
+    const bool rows = K == 0 || cell;
+    const long long aslab = rows ? 3LL * Q * nx : (long long)RT1 * 16 * 3 * nx;
     for (long long it = blockIdx.x; it < items; it += gridDim.x) {
         const long long row = it / (n * n);
         const int qbc = (int)(it - row * (n * n)), qb = qbc % n, qc = qbc / n;
@@ -1175,18 +1174,18 @@ __global__ __launch_bounds__(ACC_THREADS) void accel_cache_kernel(const double *
 #pragma unroll
                 for (int c = 0; c < 3; c++) acc[c] += P[m][c][0] * er - P[m][c][1] * ei;
             }
-            if constexpr (K == 0) {  // the finite-volume kernel's compact layout [component][x]
+            const int rho = qa + n * qb + n * n * qc;
+            if (rows) {  // [component][point][x]
 #pragma unroll
-                for (int c = 0; c < 3; c++) orow[(long long)c * nx + ix] = (S)acc[c];
+                for (int c = 0; c < 3; c++) orow[(long long)(c * Q + rho) * nx + ix] = (S)acc[c];
                 continue;
             }
-            const int rho = qa + n * qb + n * n * qc;
             const int t = rho / 16, rr = rho % 16;
             const int g = F64 ? rr % 4 : rr / 4, r = F64 ? rr / 4 : rr % 4;  // result lane group and register
 #pragma unroll
             for (int c = 0; c < 3; c++) orow[(((long long)(t * 3 + c) * 4 + g) * nx + ix) * 4 + r] = (S)acc[c];
         }
-        if (K > 0 && qbc == 0 && RT1 * 16 > Q) {  // the padding rows of the last tile
+        if (!rows && qbc == 0 && RT1 * 16 > Q) {  // the padding rows of the last tile
             for (int j = threadIdx.x; j < (RT1 * 16 - Q) * nx; j += ACC_THREADS) {
                 const int rho = Q + j / nx, ix = j % nx;
                 const int t = rho / 16, rr = rho % 16;
@@ -1201,27 +1200,27 @@ __global__ __launch_bounds__(ACC_THREADS) void accel_cache_kernel(const double *
 
 template <int K>
 static hipError_t launch_accel_k(int prec, const double *modes, int nmodes, int nx, int ny, int nz, long long nc,
-                                 const GaussNodes &xg, int z0, int nzg, void *out, hipStream_t s) {
+                                 const GaussNodes &xg, int z0, int nzg, int cell, void *out, hipStream_t s) {
     (void)nc;
     const long long items = (long long)ny * nz * (K + 1) * (K + 1);
     const long long nb = items < (1LL << 30) ? items : (1LL << 30);
     if (prec == DG_FP64)
         hipLaunchKernelGGL((accel_cache_kernel<K, double>), dim3(nb), dim3(ACC_THREADS), 0, s, modes, nmodes, nx, ny,
-                           nz, xg, z0, nzg, (double *)out);
+                           nz, xg, z0, nzg, cell, (double *)out);
     else
         hipLaunchKernelGGL((accel_cache_kernel<K, float>), dim3(nb), dim3(ACC_THREADS), 0, s, modes, nmodes, nx, ny,
-                           nz, xg, z0, nzg, (float *)out);
+                           nz, xg, z0, nzg, cell, (float *)out);
     return hipGetLastError();
 }
 
-hipError_t launch_accel_cache(int k, int prec, const double *modes, int nmodes, int nx, int ny, int nz, long long nc,
+hipError_t launch_accel_cache(int k, int prec, bool cell, const double *modes, int nmodes, int nx, int ny, int nz, long long nc,
                               const GaussNodes &xg, int z0, int nzg, void *out, hipStream_t s) {
     switch (k) {
-        case 0: return launch_accel_k<0>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, out, s);
-        case 1: return launch_accel_k<1>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, out, s);
-        case 2: return launch_accel_k<2>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, out, s);
-        case 3: return launch_accel_k<3>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, out, s);
-        case 4: return launch_accel_k<4>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, out, s);
+        case 0: return launch_accel_k<0>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, cell, out, s);
+        case 1: return launch_accel_k<1>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, cell, out, s);
+        case 2: return launch_accel_k<2>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, cell, out, s);
+        case 3: return launch_accel_k<3>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, cell, out, s);
+        case 4: return launch_accel_k<4>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, cell, out, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -1,0 +1,1077 @@
+// Stage kernel of k = 1 and k = 2 in FP64 and FP32: one cell per lane, sum factorisation on the
+// vector units (the modal DG operator of Bauer et al., arXiv 1602.09079, Sec. 2.3).
+//
+// What bounds it: vector issue.  At k = 2 an operator evaluation is about 30 HLLC solves and 27
+// volume points per cell; on 16x16 matrix-core tiles the 9 face points fill 9 of 16 rows (4 of 16 at
+// k = 1) and the padding rows are solved as well, so the matrix form issues about twice the vector
+// instructions and waits for its exchanges besides.  Here every lane works on a cell of its own and
+// no row is padding.
+//
+// Measured, one driven stage, us, matrix form -> this one: 64^3 k = 1 FP32 168 -> 31, FP64 217 -> 67;
+// k = 2 FP32 233 -> 124, FP64 455 -> 262; a 90 x 77 x 51 mesh at k = 2 FP32 707 -> 197 (14-cell blocks
+// by groups of 8 rows leave more of a ragged mesh idle than 8 x 8 tiles).  k = 2 FP32 at 64^3 issues
+// vector instructions 56% of the time with two waves per SIMD; the rest is memory and LDS latency.
+//
+// A wave owns a tile of 8 x 8 cells in x and y and sweeps a chunk of z.  Waves are independent:
+// nothing is shared between them, so there is no barrier, and a small mesh is cut into as many work
+// items as it has tiles and chunks.  Four waves on consecutive tiles along x form a workgroup, so the
+// 32-byte runs of a row that they read come from the same cache lines of one compute unit (k = 2 FP32
+// at 64^3: 133 -> 124 us against one wave per workgroup).
+//
+// Small meshes (cell_split_kernel): with a few waves in flight the time of a launch is one wave's chain
+// of dependent instructions and memory round trips.  There a workgroup takes one tile and one plane
+// and its waves one task each - x faces, y faces, the two z faces, the volume integral - and their
+// shares of R are added through LDS in a fixed order (16^3: k = 1 FP64 14.9 -> 8.8 us, k = 2 FP32
+// 30.4 -> 13.5, FP64 47.9 -> 19.3).
+//
+// Volume integral.  The integral of F_a against the gradient of the basis needs the moments of F_a
+// with the polynomials of degree k - 1 only: 1 moment at k = 1, 4 at k = 2, of the 9 distinct
+// components of the momentum and energy fluxes (the mass flux is the momentum itself, whose moments
+// are its modes).  They are collected point by point, and the derivative matrices, which are sparse
+// in this basis, are applied to them once per cell.
+//
+// Faces.  A face is described by its 2D trace modes (p, q), p + q <= k, of each field: 15 values at
+// k = 1, 30 at k = 2 instead of 20 or 45 point values.  Neighbours exchange trace modes and flux
+// moments in LDS.  Each lane solves its +x, +y and +z faces; the faces on the tile's low x and y
+// edges (16 of them) are solved point by point, spread over all 64 lanes.  The +z flux moments are
+// carried to the next plane.  Every solve takes the same arithmetic on the same modes, so a face on
+// a tile edge, which two waves solve, gets the same flux in both.
+//
+// Deviation form: the flux of the cell mean is subtracted from every volume and face flux before the
+// moments are formed.  The subtracted terms cancel exactly, and the sums run over the variation
+// inside the cell.
+
+#include <type_traits>
+
+#include "dg_device.h"
+
+namespace dgmi {
+
+// ------------------------------------------------------------------ 1D Gauss and Legendre tables
+//
+// P[u][a]: scaled Legendre polynomial sqrt(2u+1) P_u at Gauss node a; W[a]: Gauss weight / 2; E[u] =
+// sqrt(2u+1), the value at +1 (that at -1 has the sign (-1)^u).
+template <int K>
+struct Leg;
+template <>
+struct Leg<1> {
+    static constexpr double P[2][2] = {{1.0, 1.0}, {-1.0, 1.0}};
+    static constexpr double W[2] = {0.5, 0.5};
+    static constexpr double E[2] = {1.0, 1.7320508075688772935};
+};
+template <>
+struct Leg<2> {
+    // sqrt(3) x and sqrt(5) (3 x^2 - 1) / 2 at x = -sqrt(3/5), 0, sqrt(3/5)
+    static constexpr double P[3][3] = {{1.0, 1.0, 1.0},
+                                       {-1.3416407864998738178, 0.0, 1.3416407864998738178},
+                                       {0.8944271909999158786, -1.1180339887498948482, 0.8944271909999158786}};
+    static constexpr double W[3] = {0.27777777777777777778, 0.44444444444444444444, 0.27777777777777777778};
+    static constexpr double E[3] = {1.0, 1.7320508075688772935, 2.2360679774997896964};
+};
+
+// P_u at node b, b an index the compiler need not know
+template <int K, class C>
+__device__ inline C leg_at(int u, int b) {
+    C r = (C)Leg<K>::P[u][0];
+#pragma unroll
+    for (int a = 1; a <= K; a++) r = b == a ? (C)Leg<K>::P[u][a] : r;
+    return r;
+}
+
+// degrees of the modes in the graded order
+template <int K>
+struct ModeTab {
+    int u[Dims<K>::N], v[Dims<K>::N], w[Dims<K>::N];
+    constexpr ModeTab() : u(), v(), w() {
+        int l = 0;
+        for (int d = 0; d <= K; d++)
+            for (int a = d; a >= 0; a--)
+                for (int b = d - a; b >= 0; b--) {
+                    u[l] = a;
+                    v[l] = b;
+                    w[l] = d - a - b;
+                    l++;
+                }
+    }
+};
+
+// index of the 2D mode (p, q), p + q <= K
+template <int K>
+constexpr int t2(int p, int q) {
+    return p * (K + 1) - p * (p - 1) / 2 + q;
+}
+// the volume mode with degree r along the axis and (p, q) along the other two, lower axis first
+template <int K, int AX>
+constexpr int face_mode(int r, int p, int q) {
+    return AX == 0 ? mode_of<K>(r, p, q) : AX == 1 ? mode_of<K>(p, r, q) : mode_of<K>(p, q, r);
+}
+// fields seen from a face: density, normal momentum, the other two momenta, energy
+template <int AX>
+constexpr int face_field(int f) {
+    return f == 0 || f == 4 ? f : f == 1 ? 1 + AX : f == 2 ? (AX == 0 ? 2 : 1) : (AX == 2 ? 2 : 3);
+}
+
+// Reciprocal and square root of the pointwise physics.  FP64: the hardware estimate refined by two
+// Newton steps (and, for the root, one correction of the result), about half of the instructions of
+// the correctly rounded sequences, which also rescale operands this physics does not meet.
+template <class C>
+struct CellMath;
+template <>
+struct CellMath<float> {
+    __device__ static float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+    __device__ static float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
+};
+template <>
+struct CellMath<double> {
+    __device__ static double rcp(double x) {
+        double y = __builtin_amdgcn_rcp(x);
+        y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+        return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    }
+    __device__ static double sqrt_(double x) {
+        const double y = __builtin_amdgcn_rsq(x);
+        double g = x * y, h = 0.5 * y;
+        const double r = __builtin_fma(-h, g, 0.5);
+        g = __builtin_fma(g, r, g);
+        h = __builtin_fma(h, r, h);
+        g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+        g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+        return x == 0.0 ? x : g;
+    }
+};
+
+__device__ inline float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// ------------------------------------------------------------------ LDS of a wave
+//
+// Exchange planes, one per (field, 2D mode): 8 rows of 13 slots; a row is a line of cells along the
+// axis exchanged.  Slots 0..7: the tile's cells; 8, 9: the trace modes of the cells past the high x
+// and y edges; 10, 11: the flux moments of the low x and y edges.  An odd row pitch spreads the rows
+// over the banks.  Then one region that first holds the 16 low-edge faces (both sides' trace modes and
+// their point fluxes) and after them the cells' own trace modes on the face being solved.
+constexpr int CT = CELL_TILE;  // tile edge
+constexpr int CX_ROW = 13, CX_PLANE = CT * CX_ROW;
+template <int K>
+struct CellLds {
+    static constexpr int NT = (K + 1) * (K + 2) / 2, NV = NF * NT, P = Dims<K>::P;
+    static constexpr int X = NV * CX_PLANE;         // exchange planes
+    static constexpr int E = 2 * NV * 2 * CT;       // low-edge trace modes [side][value][face]
+    static constexpr int F = NF * 2 * CT * P;       // low-edge point fluxes [field][face point]
+    static constexpr int S = NV * 64;               // this tile's trace modes on the face being solved
+    // during the volume integral: the weights (k = 2, to free their registers), and the weights of the
+    // 32 cells across the tile's edges on their way in from memory
+    static constexpr bool STASH = K >= 2;
+    static constexpr int N = Dims<K>::N, W = STASH ? NF * N * 64 : 0;
+    static constexpr int RAW = X > W ? X : W, H = N / 2;
+    static constexpr int ELEMS = X + (E + F > S ? E + F : S);
+    static_assert(RAW + NF * H * 64 <= ELEMS, "the edge cells' weights fit");
+};
+
+// A copy the compiler cannot see through: addresses formed from it are formed where they are used.
+// Without it every address of the sweep is a loop invariant, hoisted, and spilled.
+template <class T>
+__device__ inline T opaque(T v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// a wave-uniform value, in scalar registers
+__device__ inline float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+__device__ inline double uniform(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
+    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | lo);
+}
+
+// Values computed up to here stay here: the compiler otherwise sinks whole phases of arithmetic past
+// the memory operations of the following ones, with their inputs live (and spilled) in between.
+template <class T, int A, int B>
+__device__ inline void pin(T (&v)[A][B]) {
+#pragma unroll
+    for (int i = 0; i < A; i++)
+#pragma unroll
+        for (int j = 0; j < B; j++) asm volatile("" : "+v"(v[i][j]));
+}
+
+// orders this wave's LDS accesses for the compiler; the LDS unit serves a wave in order
+__device__ inline void lds_order() { asm volatile("" ::: "memory"); }
+
+// Access to a state or a plane-wise array: buffer loads with a resource per z plane and 32-bit lane
+// offsets; BIG: planes of 2 GiB and more, 64-bit lane addresses.
+template <class C, bool BIG>
+struct PlaneView {
+    __amdgpu_buffer_rsrc_t rs;
+    const C *p;
+    unsigned off;  // lane offset in bytes
+    __device__ PlaneView(const void *base, long long plane, long long z, long long lane_elem) {
+        const C *b = static_cast<const C *>(base) + z * plane;
+        if constexpr (BIG) {
+            p = b + lane_elem;
+        } else {
+            rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<C *>(b), (short)0,
+                                                   (int)(unsigned)(plane * (long long)sizeof(C)), BUF_DWORD3);
+            off = opaque((unsigned)(lane_elem * (long long)sizeof(C)));
+        }
+    }
+    __device__ C get(unsigned row, unsigned nx) const {  // row: uniform
+        if constexpr (BIG)
+            return p[(long long)row * nx];
+        else
+            return bload(C(), rs, off, row * nx * (unsigned)sizeof(C));
+    }
+    __device__ void put(unsigned row, unsigned nx, C v) const {
+        if constexpr (BIG)
+            const_cast<C *>(p)[(long long)row * nx] = v;
+        else
+            bstore(v, rs, off, row * nx * (unsigned)sizeof(C));
+    }
+    // row `row` of this lane's cell into LDS by the load unit, at dst (FP64: the 64 low words, then the
+    // 64 high words); it counts as a vector memory operation and the compiler does not wait for it
+    __device__ void to_lds(unsigned row, unsigned nx, C *dst) const {
+        if constexpr (BIG) {
+            const C v = p[(long long)row * nx];
+            int *d = reinterpret_cast<int *>(dst) + (threadIdx.x & 63);
+            int u[sizeof(C) / 4];
+            __builtin_memcpy(u, &v, sizeof(C));
+            d[0] = u[0];
+            if (sizeof(C) == 8) d[64] = u[sizeof(C) / 4 - 1];
+        } else {
+#pragma unroll
+            for (int h = 0; h < (int)sizeof(C) / 4; h++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rs, (__attribute__((address_space(3))) void *)(reinterpret_cast<int *>(dst) + 64 * h), 4, off,
+                    row * nx * (unsigned)sizeof(C) + 4 * h, 0, 0);
+        }
+    }
+};
+
+// a value that to_lds put down: d points at its low word
+__device__ inline float from_lds(const int *d, float) { return __int_as_float(d[0]); }
+__device__ inline double from_lds(const int *d, double) {
+    return __longlong_as_double(((long long)d[64] << 32) | (unsigned)d[0]);
+}
+
+template <int K, class C>
+constexpr int cell_waves() { return K == 1 ? (sizeof(C) == 8 ? 1 : 3) : (sizeof(C) == 8 ? 1 : 2); }
+
+// Waves of a workgroup that splits one tile and plane by task (small meshes): the x faces, the y
+// faces, the two z faces, and the volume integral; at k = 2 in FP32 one Gauss plane of it each (in
+// FP64 a fifth wave would halve the registers of all).
+template <int K, class C>
+struct CellSplit {
+    static constexpr int VOL = 3, NVOL = K == 1 || sizeof(C) == 8 ? 1 : 3, WAVES = VOL + NVOL;
+    using LD = CellLds<K>;
+    static constexpr int ZS = 2 * LD::S, RS = NF * Dims<K>::N * 64;  // z-face modes, a wave's share of R
+    static_assert(ZS >= RS && LD::ELEMS >= RS, "the shares of R fit the regions of their waves");
+    // element offset of a wave's region; the first volume wave keeps its share in registers
+    static __device__ int base(int w) {
+        return w < 2 ? w * LD::ELEMS : w <= VOL ? 2 * LD::ELEMS : 2 * LD::ELEMS + ZS + (w - VOL - 1) * RS;
+    }
+    static constexpr int ELEMS = 2 * LD::ELEMS + ZS + (NVOL - 1) * RS;
+};
+
+template <int K, class C, bool FORCE, int RS, bool BIG, bool SPLIT>
+__device__ __forceinline__ void cell_stage(const StageArgs &a) {
+    using L = Leg<K>;
+    using M = CellMath<C>;
+    using LD = CellLds<K>;
+    constexpr int N = Dims<K>::N, n = K + 1, P = Dims<K>::P, NT = LD::NT, NV = LD::NV;
+    constexpr int NL = K * (K + 1) * (K + 2) / 6;  // modes of degree <= k - 1
+    constexpr ModeTab<K> T;
+    struct PR {
+        __device__ static C rcp(C x) { return M::rcp(x); }
+        __device__ static C sqrt_(C x) { return M::sqrt_(x); }
+    };
+    extern __shared__ __attribute__((aligned(16))) char lds_all[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    C *const lds0 = reinterpret_cast<C *>(lds_all);
+    C *const lds = lds0 + (SPLIT ? CellSplit<K, C>::base(wave) : wave * LD::ELEMS);
+    C *const lx = lds, *const le = lds + LD::X, *const lf = le + LD::E;
+
+    const int lane = threadIdx.x & 63, cx = lane & 7, cy = lane >> 3;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const unsigned unx = (unsigned)nx;
+    // items in 8 contiguous ranges by workgroup id modulo 8 (one per XCD), so neighbouring tiles share
+    // the L2 their edge cells are read through
+    long long item;
+    {
+        const int per = SPLIT ? 1 : a.wgw;  // items per workgroup
+        const long long bid = blockIdx.x, nwg = (a.nitems + per - 1) / per;
+        const long long lo = nwg / 8, extra = nwg % 8;
+        const int xcd = (int)(bid & 7);
+        item = ((bid >> 3) + xcd * lo + (xcd < extra ? xcd : extra)) * per + (SPLIT ? 0 : wave);
+    }
+    if (item >= a.nitems) return;
+    const int ntx = a.nbx, nty = (ny + CT - 1) / CT;
+    const int bx = (int)(item % ntx);
+    const long long rest = item / ntx;
+    const int by = (int)(rest % nty), zc = (int)(rest / nty);
+    const int x0 = bx * CT, y0t = by * CT;
+    const int zlen = SPLIT ? 1 : a.zlen;
+    const int z0 = zc * zlen, z1 = z0 + zlen < nz ? z0 + zlen : nz;
+    // lanes past the end of a ragged tile take the cells the periodic mesh continues with
+    const int ix = (x0 + cx) % nx, iy = (y0t + cy) % ny;
+    const bool keep = x0 + cx < nx && y0t + cy < ny;
+    const long long plane = (long long)NF * N * nx * ny;
+    const long long cell = (long long)iy * NF * N * nx + ix;
+    // edge cell of lanes 0..31 (and again of 32..63): low x, high x, low y, high y
+    long long ecell;
+    {
+        const int eg = (lane >> 3) & 3, ej = lane & 7;
+        const int ex = eg == 0 ? (x0 + nx - 1) % nx : eg == 1 ? (x0 + CT) % nx : (x0 + ej) % nx;
+        const int ey = eg == 2 ? (y0t + ny - 1) % ny : eg == 3 ? (y0t + CT) % ny : (y0t + ej) % ny;
+        ecell = (long long)ey * NF * N * nx + ex;
+    }
+    const C *yin = static_cast<const C *>(a.yin);
+    // z plane zz of the input, across the ends from the halo planes or periodic
+    auto in_plane = [&](int zz, long long &zi) -> const C * {
+        zi = 0;
+        if (a.halo_lo && zz < 0) return static_cast<const C *>(a.halo_lo);
+        if (a.halo_hi && zz >= nz) return static_cast<const C *>(a.halo_hi);
+        zi = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
+        return yin;
+    };
+    const C gam = uniform((C)a.gamma), g1 = uniform(gam - C(1));
+    double dtd = a.dt;
+    if (a.rate) dtd = a.dtfac / a.rate[0];
+    const C dt = uniform((C)dtd);
+    if (a.tacc && blockIdx.x == 0 && threadIdx.x == 0) a.tacc[0] += dtd;
+    const C ih[3] = {uniform((C)a.ih[0]), uniform((C)a.ih[1]), uniform((C)a.ih[2])};
+
+    C w[NF][N], R[NF][N], mz[NF][NT];  // weights, operator, flux moments of the face below
+
+    auto load_cells = [&](int zz) {
+        long long zi;
+        const C *b = in_plane(zz, zi);
+        const PlaneView<C, BIG> pv(b, plane, zi, cell);
+#pragma unroll
+        for (int i = 0; i < NF; i++)
+#pragma unroll
+            for (int l = 0; l < N; l++) w[i][l] = pv.get(i * N + l, unx);
+    };
+    // trace modes of this lane's cell on a face (sgn = -1, +1), fields as seen from the face
+    auto trace = [&](auto ax_c, auto sgn_c, C t[NF][NT]) {
+        constexpr int AX = decltype(ax_c)::value, SG = decltype(sgn_c)::value;
+#pragma unroll
+        for (int f = 0; f < NF; f++)
+#pragma unroll
+            for (int p = 0; p <= K; p++)
+#pragma unroll
+                for (int q = 0; q <= K - p; q++) {
+                    C s = w[face_field<AX>(f)][face_mode<K, AX>(0, p, q)];
+#pragma unroll
+                    for (int r = 1; r <= K - p - q; r++)
+                        s = fma_((C)((SG < 0 && (r & 1)) ? -L::E[r] : L::E[r]),
+                                 w[face_field<AX>(f)][face_mode<K, AX>(r, p, q)], s);
+                    t[f][t2<K>(p, q)] = s;
+                }
+    };
+    // flux of the cell mean along an axis, fields as seen from the face
+    auto mean_flux = [&](auto ax_c, C F[NF]) {
+        constexpr int AX = decltype(ax_c)::value;
+        C q[NF];
+#pragma unroll
+        for (int f = 0; f < NF; f++) q[f] = w[face_field<AX>(f)][0];
+        const C inv = M::rcp(q[0]), u = q[1] * inv;
+        const C p = g1 * (q[4] - C(0.5) * ((q[1] * q[1] + q[2] * q[2] + q[3] * q[3]) * inv));
+        F[0] = q[1];
+        F[1] = q[1] * u + p;
+        F[2] = q[2] * u;
+        F[3] = q[3] * u;
+        F[4] = (q[4] + p) * u;
+    };
+    auto solve = [&](const C qL[NF], const C qR[NF], C F[NF]) {
+        if constexpr (RS == 1)
+            exact_rs<PR, 0>(qL, qR, gam, F);
+        else
+            hllc<PR, 0>(qL, qR, gam, F);
+    };
+    // one row (second-axis node b) of a face's modes: coefficients along the last axis
+    auto row_of = [&](const C *tp, int stride, const C pb[n], C o[n]) {
+#pragma unroll
+        for (int q = 0; q <= K; q++) {
+            C s = tp[t2<K>(0, q) * stride];
+#pragma unroll
+            for (int p = 1; p <= K - q; p++) s = fma_(pb[p], tp[t2<K>(p, q) * stride], s);
+            o[q] = s;
+        }
+    };
+    auto point_of = [&](const C o[n], const C pc[n]) -> C {
+        C s = o[0];
+#pragma unroll
+        for (int q = 1; q <= K; q++) s = fma_(pc[q], o[q], s);
+        return s;
+    };
+    // the same at node c, known at compile time: terms whose coefficient is zero drop out
+    auto point_at = [&](const C o[n], int c) -> C {
+        C s = o[0];
+#pragma unroll
+        for (int q = 1; q <= K; q++)
+            if (L::P[q][c] != 0.0) s = fma_((C)L::P[q][c], o[q], s);
+        return s;
+    };
+    // moments of a face's point fluxes: row b's contribution, from its moments s along the last axis
+    auto add_row = [&](C m[NT], const C s[n], C wb, const C pb[n]) {
+#pragma unroll
+        for (int q = 0; q <= K; q++) {
+            const C t = wb * s[q];
+            m[t2<K>(0, q)] += t;
+#pragma unroll
+            for (int p = 1; p <= K - q; p++) m[t2<K>(p, q)] = fma_(pb[p], t, m[t2<K>(p, q)]);
+        }
+    };
+    // the face between this lane's cell (trace modes at lp) and the cell above (modes at rp, value
+    // stride rs), both in LDS: flux moments, the flux F0 subtracted at the points
+    auto face = [&](const C *lp, const C *rp, auto rs_c, const C F0[NF], C m[NF][NT]) {
+        constexpr int RSTR = decltype(rs_c)::value;
+#pragma unroll
+        for (int f = 0; f < NF; f++)
+#pragma unroll
+            for (int t = 0; t < NT; t++) m[f][t] = C(0);
+#pragma unroll (K == 1 ? 2 : 1)
+        for (int b = 0; b < n; b++) {
+            C pb[n], ol[NF][n], orr[NF][n], s[NF][n];
+            pb[0] = C(1);
+#pragma unroll
+            for (int p = 1; p <= K; p++) pb[p] = leg_at<K, C>(p, b);
+            C wb = (C)L::W[0];
+            if (K == 2) wb = b == 1 ? (C)L::W[1] : wb;
+#pragma unroll
+            for (int f = 0; f < NF; f++) {
+                row_of(lp + f * NT * 64, 64, pb, ol[f]);
+                row_of(rp + f * NT * RSTR, RSTR, pb, orr[f]);
+#pragma unroll
+                for (int q = 0; q <= K; q++) s[f][q] = C(0);
+            }
+#pragma unroll
+            for (int c = 0; c < n; c++) {
+                C qL[NF], qR[NF], F[NF];
+#pragma unroll
+                for (int f = 0; f < NF; f++) {
+                    qL[f] = point_at(ol[f], c);
+                    qR[f] = point_at(orr[f], c);
+                }
+                solve(qL, qR, F);
+#pragma unroll
+                for (int f = 0; f < NF; f++) {
+                    const C d = F[f] - F0[f];
+#pragma unroll
+                    for (int q = 0; q <= K; q++)
+                        if (L::P[q][c] != 0.0) s[f][q] = fma_((C)(L::W[c] * L::P[q][c]), d, s[f][q]);
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < NF; f++) add_row(m[f], s[f], wb, pb);
+        }
+    };
+    // the flux moments m of one face into R (side: +1 high face, -1 low face)
+    auto lift = [&](auto ax_c, auto sgn_c, const C m[NF][NT]) {
+        constexpr int AX = decltype(ax_c)::value, SG = decltype(sgn_c)::value;
+#pragma unroll
+        for (int f = 0; f < NF; f++)
+#pragma unroll
+            for (int p = 0; p <= K; p++)
+#pragma unroll
+                for (int q = 0; q <= K - p; q++) {
+                    const C v = (SG > 0 ? ih[AX] : -ih[AX]) * m[f][t2<K>(p, q)];
+#pragma unroll
+                    for (int r = 0; r <= K - p - q; r++) {
+                        C &o = R[face_field<AX>(f)][face_mode<K, AX>(r, p, q)];
+                        if (r == 0)
+                            o += v;
+                        else
+                            o = fma_((C)((SG < 0 && (r & 1)) ? -L::E[r] : L::E[r]), v, o);
+                    }
+                }
+    };
+    auto put_modes = [&](C *dst, int stride, const C t[NF][NT]) {
+#pragma unroll
+        for (int f = 0; f < NF; f++)
+#pragma unroll
+            for (int j = 0; j < NT; j++) dst[(f * NT + j) * stride] = t[f][j];
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using PLUS = std::integral_constant<int, 1>;
+    using MINUS = std::integral_constant<int, -1>;
+
+    // the weights of the 32 cells across the tile's edges (lanes 0..31: low x, high x, low y, high y;
+    // lanes 32..63 take the second half of the modes), requested before the volume integral
+    auto request_edges = [&](int z) {
+        const int el = opaque(lane);
+        const PlaneView<C, BIG> pv(yin, plane, z, ecell + (long long)(el >> 5) * LD::H * nx);
+        C *dst = lds + LD::RAW;
+        asm volatile("" : "+s"(dst));
+#pragma unroll
+        for (int i = 0; i < NF; i++)
+#pragma unroll
+            for (int l = 0; l < LD::H; l++) pv.to_lds(i * N + l, unx, dst + (i * LD::H + l) * 64);
+    };
+    // trace modes of the edge cells and of the tile's own low-edge cells, then the fluxes of the 16
+    // low-edge faces and their moments
+    auto edges = [&](int z) {
+        const int ol = opaque(lane), cx = ol & 7, cy = ol >> 3;
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the edge cells have landed
+        lds_order();
+        C ew[NF][N];  // (lanes 32..63 read the same cells and drop them)
+        {
+            const bool ay = ol & (2 * CT);  // normal axis y
+            const int *src = reinterpret_cast<const int *>(lds + LD::RAW);
+            int mo[N];  // word offset of the mode with degrees (r, p, q) as seen from the face
+#pragma unroll
+            for (int l = 0; l < N; l++) {  // (r, p, q) = (u, v, w) of the x faces
+                const int ly = face_mode<K, 1>(T.u[l], T.v[l], T.w[l]);
+                constexpr int WD = sizeof(C) / 4 * 64;
+                const int ax_ = (l % LD::H) * WD + (l >= LD::H ? 32 : 0), ay_ = (ly % LD::H) * WD + (ly >= LD::H ? 32 : 0);
+                mo[l] = (ol & 31) + (ay ? ay_ : ax_);
+            }
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++)
+                    ew[i][l] = from_lds(src + i * LD::H * (int)(sizeof(C) / 4) * 64 + mo[l], C());
+        }
+        lds_order();
+        if (ol < 4 * CT) {
+            const int eg = ol >> 3, ej = ol & 7;
+            const bool ay = eg >= 2;  // normal axis y
+            const C sg = (eg & 1) ? C(-1) : C(1);
+            const int stride = (eg & 1) ? CX_PLANE : 2 * CT;
+            const int d0 = opaque((eg & 1) ? ej * CX_ROW + CT + (ay ? 1 : 0) : LD::X + (ay ? CT : 0) + ej);
+            C c1[n];
+#pragma unroll
+            for (int r = 0; r <= K; r++) c1[r] = (r & 1) ? sg * (C)L::E[r] : (C)L::E[r];
+#pragma unroll
+            for (int i = 0; i < NF; i++) {
+                const int f = i == 1 ? (ay ? 2 : 1) : i == 2 ? (ay ? 1 : 2) : i;
+                C *dst = lds + d0 + f * NT * stride;
+#pragma unroll
+                for (int p = 0; p <= K; p++)
+#pragma unroll
+                    for (int q = 0; q <= K - p; q++) {
+                        C s = ew[i][mode_of<K>(0, p, q)];
+#pragma unroll
+                        for (int r = 1; r <= K - p - q; r++) s = fma_(c1[r], ew[i][mode_of<K>(r, p, q)], s);
+                        dst[t2<K>(p, q) * stride] = s;
+                    }
+            }
+        }
+        {
+            C t[NF][NT];
+            trace(I0{}, MINUS{}, t);
+            if (cx == 0) put_modes(le + opaque(NV * 2 * CT + cy), 2 * CT, t);
+            trace(I1{}, MINUS{}, t);
+            if (cy == 0) put_modes(le + opaque(NV * 2 * CT + CT + cx), 2 * CT, t);
+        }
+        lds_order();
+#pragma unroll 1
+        for (int e = opaque(lane); e < 2 * CT * P; e += 64) {
+            const int fc = e / P, pt = e - fc * P, b = pt / n, c = pt - b * n;
+            C pb[n], pc[n], qL[NF], qR[NF], F[NF];
+            pb[0] = pc[0] = C(1);
+#pragma unroll
+            for (int p = 1; p <= K; p++) {
+                pb[p] = leg_at<K, C>(p, b);
+                pc[p] = leg_at<K, C>(p, c);
+            }
+#pragma unroll
+            for (int f = 0; f < NF; f++) {
+                C o[n];
+                row_of(le + f * NT * 2 * CT + fc, 2 * CT, pb, o);
+                qL[f] = point_of(o, pc);
+                row_of(le + (NV + f * NT) * 2 * CT + fc, 2 * CT, pb, o);
+                qR[f] = point_of(o, pc);
+            }
+            solve(qL, qR, F);
+#pragma unroll
+            for (int f = 0; f < NF; f++) lf[f * 2 * CT * P + e] = F[f];
+        }
+        lds_order();
+#pragma unroll 1
+        for (int e = opaque(lane); e < 2 * CT * NF; e += 64) {  // (face, field)
+            const int f = e / (2 * CT), fc = e - f * 2 * CT;
+            C m[NT];
+#pragma unroll
+            for (int t = 0; t < NT; t++) m[t] = C(0);
+#pragma unroll
+            for (int b = 0; b < n; b++) {
+                C pb[n], s[n];
+#pragma unroll
+                for (int p = 0; p <= K; p++) {
+                    pb[p] = (C)L::P[p][b];
+                    s[p] = C(0);
+                }
+#pragma unroll
+                for (int c = 0; c < n; c++) {
+                    const C d = lf[f * 2 * CT * P + fc * P + b * n + c];
+#pragma unroll
+                    for (int q = 0; q <= K; q++)
+                        if (L::P[q][c] != 0.0) s[q] = fma_((C)(L::W[c] * L::P[q][c]), d, s[q]);
+                }
+                add_row(m, s, (C)L::W[b], pb);
+            }
+            C *dst = lx + f * NT * CX_PLANE + (fc & 7) * CX_ROW + (fc >= CT ? 11 : 10);
+#pragma unroll
+            for (int t = 0; t < NT; t++) dst[t * CX_PLANE] = m[t];
+        }
+        lds_order();
+    };
+    // the +x or +y face of every lane; both of its cells take the moments
+    auto side = [&](auto ax_c) {
+        constexpr int AX = decltype(ax_c)::value;
+        const int ol = opaque(lane), me = AX == 0 ? ol & 7 : ol >> 3, ln = AX == 0 ? ol >> 3 : ol & 7;
+        C *const row = lx + ln * CX_ROW;
+        C F0[NF], m[NF][NT];
+        {
+            C t[NF][NT];
+            trace(ax_c, MINUS{}, t);
+            put_modes(row + me, CX_PLANE, t);
+            trace(ax_c, PLUS{}, t);
+            put_modes(le + opaque(lane), 64, t);
+        }
+        lds_order();
+        mean_flux(ax_c, F0);
+        face(le + opaque(lane), row + (me == CT - 1 ? CT + AX : me + 1), std::integral_constant<int, CX_PLANE>{}, F0, m);
+        lift(ax_c, PLUS{}, m);
+        lds_order();
+        // the moments as absolute fluxes for the cell above
+#pragma unroll
+        for (int f = 0; f < NF; f++) m[f][0] += F0[f];
+        put_modes(row + me, CX_PLANE, m);
+        lds_order();
+        const C *src = row + (me == 0 ? 10 + AX : me - 1);
+#pragma unroll
+        for (int f = 0; f < NF; f++)
+#pragma unroll
+            for (int j = 0; j < NT; j++) m[f][j] = src[(f * NT + j) * CX_PLANE];
+#pragma unroll
+        for (int f = 0; f < NF; f++) m[f][0] -= F0[f];
+        lift(ax_c, MINUS{}, m);
+        pin(R);
+        lds_order();
+    };
+    // volume integral and driving source of the Gauss planes A0 <= qa < A1 along x
+    auto volume = [&](int z, auto a0_c, auto a1_c) {
+        constexpr int A0 = decltype(a0_c)::value, A1 = decltype(a1_c)::value;
+        constexpr bool STASH = LD::STASH && !SPLIT;
+        C mu[9][NL];  // moments of the fluxes xx xy xz yy yz zz of the momentum, x y z of the energy
+#pragma unroll
+        for (int j = 0; j < 9; j++)
+#pragma unroll
+            for (int l = 0; l < NL; l++) mu[j][l] = C(0);
+        C fb[9];
+        {
+            const C inv = M::rcp(w[0][0]);
+            const C u = w[1][0] * inv, v = w[2][0] * inv, ww = w[3][0] * inv;
+            const C p = g1 * (w[4][0] - C(0.5) * (w[1][0] * u + w[2][0] * v + w[3][0] * ww));
+            const C ep = w[4][0] + p;
+            fb[0] = w[1][0] * u + p;
+            fb[1] = w[1][0] * v;
+            fb[2] = w[1][0] * ww;
+            fb[3] = w[2][0] * v + p;
+            fb[4] = w[2][0] * ww;
+            fb[5] = w[3][0] * ww + p;
+            fb[6] = ep * u;
+            fb[7] = ep * v;
+            fb[8] = ep * ww;
+        }
+        // driving acceleration at the points of a column, requested two columns ahead
+        const long long aplane = 3LL * n * n * n * nx * ny;
+        C ac[3][3][n];
+        auto accel = [&](int col, C o[3][n]) {
+            const PlaneView<C, BIG> av(a.acache, aplane, z, (long long)iy * 3 * n * n * n * nx + ix);
+            const int qa = col / n, qb = col % n;
+#pragma unroll
+            for (int c = 0; c < 3; c++)
+#pragma unroll
+                for (int qc = 0; qc < n; qc++) o[c][qc] = av.get(c * n * n * n + (qc * n + qb) * n + qa, unx);
+        };
+        if constexpr (FORCE) {
+            accel(A0 * n, ac[(A0 * n) % 3]);
+            accel(A0 * n + 1, ac[(A0 * n + 1) % 3]);
+        }
+        if constexpr (STASH) {
+            lds_order();
+            C *const wp = lds + opaque(lane);
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++) wp[(i * N + l) * 64] = w[i][l];
+            lds_order();
+        }
+        const C *const ws = lds + opaque(lane);  // the weights' copies (STASH)
+#pragma unroll
+        for (int qa = A0; qa < A1; qa++) {
+            C Mx[NF][NT];
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int v = 0; v <= K; v++)
+#pragma unroll
+                    for (int ww = 0; ww <= K - v; ww++) {
+                        auto wt = [&](int l) { return STASH ? ws[(i * N + l) * 64] : w[i][l]; };
+                        C s = wt(mode_of<K>(0, v, ww));
+#pragma unroll
+                        for (int u = 1; u <= K - v - ww; u++)
+                            if (L::P[u][qa] != 0.0) s = fma_((C)L::P[u][qa], wt(mode_of<K>(u, v, ww)), s);
+                        Mx[i][t2<K>(v, ww)] = s;
+                    }
+#pragma unroll
+            for (int qb = 0; qb < n; qb++) {
+                C Z[NF][n], mq[9][K], sq[4][n];
+                const int col = qa * n + qb;
+                if constexpr (FORCE)
+                    if (col + 2 < A1 * n) accel(col + 2, ac[(col + 2) % 3]);
+#pragma unroll
+                for (int i = 0; i < NF; i++)
+#pragma unroll
+                    for (int ww = 0; ww <= K; ww++) {
+                        C s = Mx[i][t2<K>(0, ww)];
+#pragma unroll
+                        for (int v = 1; v <= K - ww; v++)
+                            if (L::P[v][qb] != 0.0) s = fma_((C)L::P[v][qb], Mx[i][t2<K>(v, ww)], s);
+                        Z[i][ww] = s;
+                    }
+#pragma unroll
+                for (int j = 0; j < 9; j++)
+#pragma unroll
+                    for (int m = 0; m < K; m++) mq[j][m] = C(0);
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+#pragma unroll
+                    for (int m = 0; m < n; m++) sq[j][m] = C(0);
+#pragma unroll
+                for (int qc = 0; qc < n; qc++) {
+                    C q[NF];
+#pragma unroll
+                    for (int i = 0; i < NF; i++) {
+                        C s = Z[i][0];
+#pragma unroll
+                        for (int ww = 1; ww <= K; ww++)
+                            if (L::P[ww][qc] != 0.0) s = fma_((C)L::P[ww][qc], Z[i][ww], s);
+                        q[i] = s;
+                    }
+                    const C inv = M::rcp(q[0]);
+                    const C u = q[1] * inv, v = q[2] * inv, ww = q[3] * inv;
+                    const C p = g1 * (q[4] - C(0.5) * (q[1] * u + q[2] * v + q[3] * ww));
+                    const C ep = q[4] + p;
+                    C f[9];
+                    f[0] = q[1] * u + p;
+                    f[1] = q[1] * v;
+                    f[2] = q[1] * ww;
+                    f[3] = q[2] * v + p;
+                    f[4] = q[2] * ww;
+                    f[5] = q[3] * ww + p;
+                    f[6] = ep * u;
+                    f[7] = ep * v;
+                    f[8] = ep * ww;
+#pragma unroll
+                    for (int j = 0; j < 9; j++) {
+                        const C d = f[j] - fb[j];
+#pragma unroll
+                        for (int m = 0; m < K; m++)
+                            if (L::P[m][qc] != 0.0) mq[j][m] = fma_((C)(L::W[qc] * L::P[m][qc]), d, mq[j][m]);
+                    }
+                    if constexpr (FORCE) {
+                        C sv[4];
+#pragma unroll
+                        for (int c = 0; c < 3; c++) sv[c] = q[0] * ac[col % 3][c][qc];
+                        sv[3] = q[1] * ac[col % 3][0][qc] + q[2] * ac[col % 3][1][qc] +
+                                q[3] * ac[col % 3][2][qc];
+#pragma unroll
+                        for (int j = 0; j < 4; j++)
+#pragma unroll
+                            for (int m = 0; m < n; m++)
+                                if (L::P[m][qc] != 0.0) sq[j][m] = fma_((C)(L::W[qc] * L::P[m][qc]), sv[j], sq[j][m]);
+                    }
+                }
+                // this (x, y) column into the moments of degree <= k - 1; the source into R
+#pragma unroll
+                for (int l = 0; l < NL; l++) {
+                    const C cf = (C)(L::W[qa] * L::W[qb] * L::P[T.u[l]][qa] * L::P[T.v[l]][qb]);
+#pragma unroll
+                    for (int j = 0; j < 9; j++)
+                        if (L::P[T.u[l]][qa] * L::P[T.v[l]][qb] != 0.0) mu[j][l] = fma_(cf, mq[j][T.w[l]], mu[j][l]);
+                }
+                if constexpr (FORCE) {
+#pragma unroll
+                    for (int l = 0; l < N; l++) {
+                        const C cf = (C)(-L::W[qa] * L::W[qb] * L::P[T.u[l]][qa] * L::P[T.v[l]][qb]);
+#pragma unroll
+                        for (int j = 0; j < 4; j++)
+                            if (L::P[T.u[l]][qa] * L::P[T.v[l]][qb] != 0.0)
+                                R[1 + j][l] = fma_(cf, sq[j][T.w[l]], R[1 + j][l]);
+                    }
+                    pin(R);
+                }
+                pin(mu);
+            }
+        }
+        if constexpr (STASH) {
+            lds_order();
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++) w[i][l] = ws[(i * N + l) * 64];
+        }
+        // R_l -= 2/h_a sum over l' of d(l, l') mu_l', l' = l with a lower degree of the other parity along
+        // axis a: d = sqrt((2u+1)(2u'+1)); the mass flux's moments are the momentum's modes (mode 0 is the
+        // subtracted mean flux)
+        constexpr int TENS[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
+#pragma unroll
+        for (int l = 1; l < N; l++)
+#pragma unroll
+            for (int ax = 0; ax < 3; ax++) {
+                const int deg = ax == 0 ? T.u[l] : ax == 1 ? T.v[l] : T.w[l];
+#pragma unroll
+                for (int e = deg - 1; e >= 0; e -= 2) {
+                    const int lp = ax == 0 ? mode_of<K>(e, T.v[l], T.w[l])
+                                           : ax == 1 ? mode_of<K>(T.u[l], e, T.w[l]) : mode_of<K>(T.u[l], T.v[l], e);
+                    const C d = (C)(-2.0 * L::E[deg] * L::E[e]) * ih[ax];
+                    if (A0 == 0 && lp > 0) R[0][l] = fma_(d, w[1 + ax][lp], R[0][l]);
+#pragma unroll
+                    for (int i = 0; i < 3; i++) R[1 + i][l] = fma_(d, mu[TENS[i][ax]][lp], R[1 + i][l]);
+                    R[4][l] = fma_(d, mu[6 + ax][lp], R[4][l]);
+                }
+            }
+    };
+
+    // the +z face of the plane in w, whose mean flux is F0: flux moments mz relative to F0; the next
+    // plane's cells are left in w
+    auto zface = [&](int z, C F0[NF]) {
+        mean_flux(I2{}, F0);
+        {
+            C t[NF][NT];
+            trace(I2{}, PLUS{}, t);
+            put_modes(lds + LD::S + opaque(lane), 64, t);
+            load_cells(z + 1);
+            trace(I2{}, MINUS{}, t);
+            put_modes(lx + opaque(lane), 64, t);
+        }
+        lds_order();
+        face(lds + LD::S + opaque(lane), lx + opaque(lane), std::integral_constant<int, 64>{}, F0, mz);
+        lds_order();
+    };
+
+    // the closure's correction, the stage update and the store of the plane in R
+    auto finish = [&](int z) {
+        const PlaneView<C, BIG> po(a.out, plane, z, cell);
+        if (K == 1 && a.corr) {  // learned closure: dy/dt = -R + c
+            const PlaneView<C, BIG> pc(a.corr, plane, z, cell);
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++)
+                    R[i][l] -= pc.get(i * N + l, unx) - (l == 0 ? (C)a.cmean[i] : C(0));
+        }
+        // out = a y0 + b (yin - dt R); the stage input is read again (through the caches) rather than held
+        // across the faces
+        auto combine = [&](auto with0) {
+            const C bb = uniform((C)a.b), aa = uniform((C)a.a);
+            const PlaneView<C, BIG> p1(yin, plane, z, cell), p0(a.y0, plane, z, cell);
+            C v[NF][N], v0[NF][N];
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++) {
+                    if (with0) v0[i][l] = p0.get(i * N + l, unx);
+                    v[i][l] = p1.get(i * N + l, unx);
+                }
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++) {
+                    R[i][l] = bb * (v[i][l] - dt * R[i][l]);
+                    if (with0) R[i][l] = aa * v0[i][l] + R[i][l];
+                }
+        };
+        if (a.mode != 0) {
+            if (a.a != 0.0)
+                combine(std::true_type{});
+            else
+                combine(std::false_type{});
+        }
+        if (keep) {
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++) po.put(i * N + l, unx, R[i][l]);
+        }
+    };
+
+    C F0[NF];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < NF; i++)
+#pragma unroll
+            for (int l = 0; l < N; l++) R[i][l] = C(0);
+    };
+    // the flux moments of the face below, absolute with respect to F0, onto this cell's mean flux
+    auto rebase = [&]() {
+#pragma unroll
+        for (int f = 0; f < NF; f++) mz[f][0] += F0[f];
+        mean_flux(I2{}, F0);
+#pragma unroll
+        for (int f = 0; f < NF; f++) mz[f][0] -= F0[f];
+    };
+    if constexpr (SPLIT) {
+        using SP = CellSplit<K, C>;
+        if (wave < 2) {
+            request_edges(z0);
+            load_cells(z0);
+            clear();
+            edges(z0);
+            if (wave == 0)
+                side(I0{});
+            else
+                side(I1{});
+        } else if (wave == 2) {
+            load_cells(z0 - 1);
+            zface(z0 - 1, F0);
+            rebase();
+            clear();
+            lift(I2{}, MINUS{}, mz);
+            pin(R);
+            zface(z0, F0);
+            lift(I2{}, PLUS{}, mz);
+        } else {
+            load_cells(z0);
+            clear();
+            if constexpr (SP::NVOL == 1)
+                volume(z0, I0{}, std::integral_constant<int, n>{});
+            else if (wave == SP::VOL)
+                volume(z0, I0{}, I1{});
+            else if (wave == SP::VOL + 1)
+                volume(z0, I1{}, I2{});
+            else
+                volume(z0, I2{}, std::integral_constant<int, 3>{});
+        }
+        if (wave != SP::VOL) {  // shares of R, in the waves' own regions
+            lds_order();
+            C *p = lds + opaque(lane);
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++) p[(i * N + l) * 64] = R[i][l];
+        }
+        __syncthreads();
+        if (wave != SP::VOL) return;
+#pragma unroll 1
+        for (int v = 0; v < SP::WAVES; v++) {
+            if (v == SP::VOL) continue;
+            const C *p = lds0 + SP::base(v) + opaque(lane);
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++) R[i][l] += p[(i * N + l) * 64];
+        }
+        finish(z0);
+    } else {
+        load_cells(z0 - 1);
+        zface(z0 - 1, F0);
+#pragma unroll 1
+        for (int z = z0; z < z1; z++) {
+            rebase();
+            clear();
+            lift(I2{}, MINUS{}, mz);
+            pin(R);
+            request_edges(z);
+            volume(z, I0{}, std::integral_constant<int, n>{});
+            pin(R);
+            edges(z);
+            side(I0{});
+            side(I1{});
+            zface(z, F0);
+            lift(I2{}, PLUS{}, mz);
+            finish(z);
+        }
+    }
+}
+
+template <int K, class C, bool FORCE, int RS, bool BIG>
+__global__ __launch_bounds__(64 * CELL_WAVES)
+    __attribute__((amdgpu_waves_per_eu(cell_waves<K, C>(), cell_waves<K, C>()))) void cell_stage_kernel(StageArgs a) {
+    cell_stage<K, C, FORCE, RS, BIG, false>(a);
+}
+
+template <int K, class C>
+constexpr int split_simd_waves() { return (CellSplit<K, C>::WAVES + 3) / 4; }
+template <int K, class C, bool FORCE, int RS>
+__global__ __launch_bounds__((64 * CellSplit<K, C>::WAVES))
+    __attribute__((amdgpu_waves_per_eu(split_simd_waves<K, C>()))) void cell_split_kernel(StageArgs a) {
+    cell_stage<K, C, FORCE, RS, false, true>(a);
+}
+
+template <int K, class C>
+constexpr int cell_lds(int waves) { return waves * CellLds<K>::ELEMS * (int)sizeof(C); }
+template <int K, class C>
+constexpr int split_lds() { return CellSplit<K, C>::ELEMS * (int)sizeof(C); }
+
+template <int K, class C, bool FORCE, int RS>
+static hipError_t launch_cell_t(const StageArgs &a, hipStream_t s) {
+    const long long plane = (long long)sizeof(C) * NF * Dims<K>::N * a.nx * a.ny;
+    const long long aplane = (long long)sizeof(C) * 3 * Dims<K>::Q * a.nx * a.ny;
+    const bool big = plane >= (1LL << 31) || (FORCE && aplane >= (1LL << 31));
+    if (a.wgw == 0) {  // one tile and plane per workgroup, split by task (small meshes, so never big planes)
+        if (big) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((cell_split_kernel<K, C, FORCE, RS>), dim3((unsigned)a.nitems),
+                           dim3(64 * CellSplit<K, C>::WAVES), (split_lds<K, C>()), s, a);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)((a.nitems + a.wgw - 1) / a.wgw)), block(64 * a.wgw);
+    if (big)
+        hipLaunchKernelGGL((cell_stage_kernel<K, C, FORCE, RS, true>), grid, block, (cell_lds<K, C>(a.wgw)), s, a);
+    else
+        hipLaunchKernelGGL((cell_stage_kernel<K, C, FORCE, RS, false>), grid, block, (cell_lds<K, C>(a.wgw)), s, a);
+    return hipGetLastError();
+}
+
+template <int K, class C>
+static hipError_t launch_cell_kc(const StageArgs &a, hipStream_t s) {
+    if (a.riemann) return a.forcing ? launch_cell_t<K, C, true, 1>(a, s) : launch_cell_t<K, C, false, 1>(a, s);
+    return a.forcing ? launch_cell_t<K, C, true, 0>(a, s) : launch_cell_t<K, C, false, 0>(a, s);
+}
+
+hipError_t launch_stage_cell(int k, int prec, const StageArgs &a, hipStream_t s) {
+    const bool f64 = prec == DG_FP64;
+    if (k == 1) return f64 ? launch_cell_kc<1, double>(a, s) : launch_cell_kc<1, float>(a, s);
+    if (k == 2) return f64 ? launch_cell_kc<2, double>(a, s) : launch_cell_kc<2, float>(a, s);
+    return hipErrorInvalidValue;
+}
+
+template <int K, class C, bool FORCE, int RS>
+static hipError_t cell_attr_t() {
+    const int lds = cell_lds<K, C>(CELL_WAVES);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&cell_stage_kernel<K, C, FORCE, RS, false>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&cell_stage_kernel<K, C, FORCE, RS, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&cell_split_kernel<K, C, FORCE, RS>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, split_lds<K, C>());
+    return e;
+}
+template <int K, class C>
+static hipError_t cell_setup_t(int *per_cu) {
+    hipError_t e = cell_attr_t<K, C, false, 0>();
+    if (e == hipSuccess) e = cell_attr_t<K, C, true, 0>();
+    if (e == hipSuccess) e = cell_attr_t<K, C, false, 1>();
+    if (e == hipSuccess) e = cell_attr_t<K, C, true, 1>();
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, cell_stage_kernel<K, C, true, 0, false>,
+                                                         64 * CELL_WAVES, (size_t)cell_lds<K, C>(CELL_WAVES));
+    return e;
+}
+// allows the kernels their LDS; per_cu: workgroups a compute unit holds
+hipError_t stage_cell_setup(int k, int prec, int *per_cu) {
+    const bool f64 = prec == DG_FP64;
+    if (k == 1) return f64 ? cell_setup_t<1, double>(per_cu) : cell_setup_t<1, float>(per_cu);
+    if (k == 2) return f64 ? cell_setup_t<2, double>(per_cu) : cell_setup_t<2, float>(per_cu);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace dgmi
