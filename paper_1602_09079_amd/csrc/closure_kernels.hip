@@ -17,6 +17,7 @@
 // built on the host from the library's own basis and Gauss rules.
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <string>
 
@@ -449,19 +450,6 @@ hipError_t launch_rowsum(const float *X, int M, int N, float *out, hipStream_t s
     return hipGetLastError();
 }
 
-// Counter-based standard normal draw for element `idx` of stream `seed`: the
-// SplitMix64 output function (Steele, Lea and Flood, 2014) of the counter gives
-// two 32-bit uniforms, the Box-Muller transform a normal deviate.
-__device__ inline float normal_draw(unsigned long long seed, unsigned long long idx) {
-    unsigned long long z = seed + 0x9E3779B97F4A7C15ull * (idx + 1ull);
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    z ^= z >> 31;
-    const float u1 = ((float)(unsigned)(z >> 40) + 1.0f) * (1.0f / 16777216.0f);  // (0, 1]
-    const float u2 = (float)(unsigned)(z & 0xffffffull) * (1.0f / 16777216.0f);   // [0, 1)
-    return sqrtf(-2.0f * logf(u1)) * __builtin_amdgcn_cosf(u2);  // cos(2 pi u2): argument in revolutions
-}
-
 // Xb[k][s] = X[rows[s]][k] (+ noise * N(0,1)) (feature-major batch), rows == nullptr: row s
 __global__ void gather_kernel(const float *X, int cols, const int *rows, int batch, float *Xb, float noise,
                               unsigned long long seed) {
@@ -507,11 +495,10 @@ hipError_t launch_mse(const float *Y, const float *T, float *dY, long long n, do
     return hipGetLastError();
 }
 
-__global__ void adam_kernel(float *p, const float *g, float *m, float *v, long long n, int step, double lr, double b1,
-                            double b2, double eps) {
+__global__ void adam_kernel(float *p, const float *g, float *m, float *v, long long n, double c1, double c2, double lr,
+                            double b1, double b2, double eps) {
     const long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
-    const double c1 = 1.0 - pow(b1, (double)step), c2 = 1.0 - pow(b2, (double)step);
     const float gj = g[j];
     const float mj = (float)b1 * m[j] + (float)(1.0 - b1) * gj;
     const float vj = (float)b2 * v[j] + (float)(1.0 - b2) * gj * gj;
@@ -522,7 +509,8 @@ __global__ void adam_kernel(float *p, const float *g, float *m, float *v, long l
 
 hipError_t launch_adam(float *p, const float *g, float *m, float *v, long long n, int step, double lr, double b1,
                        double b2, double eps, hipStream_t s) {
-    hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, g, m, v, n, step, lr, b1, b2, eps);
+    hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, g, m, v, n,
+                       1.0 - std::pow(b1, (double)step), 1.0 - std::pow(b2, (double)step), lr, b1, b2, eps);
     return hipGetLastError();
 }
 

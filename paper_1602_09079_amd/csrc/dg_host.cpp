@@ -1355,7 +1355,8 @@ size_t dg_mlp_workspace_bytes(const int32_t shape[4], int32_t batch) {
     if (!mlp_shape_ok(shape) || batch < 1) return 0;
     const size_t B = batch;
     // Xb, H1, H2, Y, Tb, dY, D2, D1 (feature-major) and a loss slot
-    return sizeof(float) * B * ((size_t)shape[0] + 2 * shape[1] + 2 * shape[2] + 3 * shape[3]) + 64;
+    const size_t b = sizeof(float) * B * ((size_t)shape[0] + 2 * shape[1] + 2 * shape[2] + 3 * shape[3]) + 64;
+    return mlp_fused_fits(shape) ? std::max(b, mlp_fused_bytes(shape, batch)) : b;
 }
 
 namespace {
@@ -1374,6 +1375,19 @@ MlpWork carve(const int32_t *sh, int B, void *work) {
     w.Tb = p; p += (size_t)sh[3] * B;
     w.dY = p;
     return w;
+}
+MlpArgs mlp_args(const int32_t *sh, const float *params, int batch, const float *x, const int32_t *rows) {
+    MlpArgs a{};
+    a.params = params;
+    a.x = x;
+    a.rows = rows;
+    a.nin = sh[0];
+    a.h1 = sh[1];
+    a.h2 = sh[2];
+    a.no = sh[3];
+    a.batch = batch;
+    a.nparams = (long long)dg_mlp_nparams(sh);
+    return a;
 }
 // C[M][B] = act(W[M][K] X[K][B] + b), feature-major activations
 hipError_t dense(const float *W, const float *b, const float *X, float *C, int M, int K, int B, int ep,
@@ -1400,6 +1414,11 @@ dg_status dg_mlp_forward(const int32_t shape[4], const float *params, int32_t ba
                          float *y, void *work, void *hip_stream) {
     if (!mlp_shape_ok(shape) || batch < 1 || !params || !x || !y || !work) return DG_ERR_ARG;
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
+    if (mlp_fused_fits(shape)) {
+        MlpArgs a = mlp_args(shape, params, batch, x, rows);
+        a.y = y;
+        return launch_mlp_fused(a, false, s) == hipSuccess ? DG_OK : DG_ERR_HIP;
+    }
     const MlpWork w = carve(shape, batch, work);
     if (launch_gather(x, shape[0], rows, batch, w.Xb, s) != hipSuccess) return DG_ERR_HIP;
     if (mlp_fwd(shape, params, batch, w, s) != hipSuccess) return DG_ERR_HIP;
@@ -1414,6 +1433,17 @@ dg_status dg_mlp_loss_grad(const int32_t shape[4], const float *params, int32_t 
     if (!mlp_shape_ok(shape) || batch < 1 || !params || !x || !target || !grad || !work || !(noise_std >= 0.0f))
         return DG_ERR_ARG;
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
+    if (mlp_fused_fits(shape)) {
+        MlpArgs a = mlp_args(shape, params, batch, x, rows);
+        a.target = target;
+        a.grad = grad;
+        a.loss = loss;
+        a.noise = noise_std;
+        a.seed = (unsigned long long)seed;
+        a.dscale = (float)(2.0 / ((double)shape[3] * batch));
+        mlp_fused_carve(a, work);
+        return launch_mlp_fused(a, true, s) == hipSuccess ? DG_OK : DG_ERR_HIP;
+    }
     const int nin = shape[0], h1 = shape[1], h2 = shape[2], no = shape[3], B = batch;
     const MlpWork w = carve(shape, B, work);
     const float *W2 = params + (size_t)h1 * nin + h1, *W3 = W2 + (size_t)h2 * h1 + h2;

@@ -290,6 +290,41 @@ hipError_t launch_restrict(int prec, const void *yf, void *yc, const double *M, 
                            hipStream_t s);
 
 // ---- training kernels
+// the fused form (mlp_fused.hip) for networks whose 16-sample tile fits in LDS
+struct MlpArgs {
+    const float *params, *x, *target;
+    const int *rows;
+    float *y, *grad;
+    double *loss;
+    int nin, h1, h2, no, batch;
+    float noise, dscale;  // input noise; 2 / (batch no)
+    unsigned long long seed;
+    long long nparams;
+    // workspace: feature-major [feature][bp] activations and signals, shares of the gradient
+    int bp, nsplit, schunk;
+    float *X, *H1, *D1, *H2, *D2, *dY, *part;
+    double *bpart, *lpart;
+};
+bool mlp_fused_fits(const int32_t sh[4]);
+size_t mlp_fused_bytes(const int32_t sh[4], int batch);
+void mlp_fused_carve(MlpArgs &a, void *work);
+hipError_t launch_mlp_fused(const MlpArgs &a, bool grad, hipStream_t s);
+
+#ifdef __HIPCC__
+// Counter-based standard normal draw for element `idx` of stream `seed`: the
+// SplitMix64 output function (Steele, Lea and Flood, 2014) of the counter gives
+// two 32-bit uniforms, the Box-Muller transform a normal deviate.
+__device__ inline float normal_draw(unsigned long long seed, unsigned long long idx) {
+    unsigned long long z = seed + 0x9E3779B97F4A7C15ull * (idx + 1ull);
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    const float u1 = ((float)(unsigned)(z >> 40) + 1.0f) * (1.0f / 16777216.0f);  // (0, 1]
+    const float u2 = (float)(unsigned)(z & 0xffffffull) * (1.0f / 16777216.0f);   // [0, 1)
+    return sqrtf(-2.0f * logf(u1)) * __builtin_amdgcn_cosf(u2);  // cos(2 pi u2): argument in revolutions
+}
+#endif
+
 enum { EP_NONE = 0, EP_TANH = 1, EP_DTANH = 2 };
 struct GemmArgs {
     const float *A, *B;
