@@ -768,6 +768,7 @@ dg_status dg_destroy(dg_ctx *c) {
     if (c->dcs) (void)hipFree(c->dcs);
     if (c->diag_bins) (void)hipFree(c->diag_bins);
     if (c->diag_partials) (void)hipFree(c->diag_partials);
+    if (c->shell_parts) (void)hipFree(c->shell_parts);
     if (c->fft) (void)hipfftDestroy(static_cast<hipfftHandle>(c->fft));
     delete c;
     return DG_OK;
@@ -1625,7 +1626,11 @@ dg_status dg_velocity_spectrum(dg_ctx *c, const void *y, int32_t S, int32_t nbin
         c->err = "dg_velocity_spectrum: hipfftSetStream failed";
         return DG_ERR_HIP;
     }
-    HIPCHK(c, launch_fill_zero(reinterpret_cast<unsigned long long *>(c->diag_bins), nbins, c->stream));
+    if (!c->shell_parts && hipMalloc(&c->shell_parts, SHELL_PARTS * sizeof(double)) != hipSuccess) {
+        c->shell_parts = nullptr;
+        c->err = "dg_velocity_spectrum: hipMalloc failed";
+        return DG_ERR_HIP;
+    }
     const double scale = 1.0 / ((double)M * M * M * (double)M * M * M);
     for (int comp = 1; comp <= 3; comp++) {
         SampleArgs a = sample_args(c, y, comp);
@@ -1639,8 +1644,9 @@ dg_status dg_velocity_spectrum(dg_ctx *c, const void *y, int32_t S, int32_t nbin
             c->err = "dg_velocity_spectrum: FFT execution failed";
             return DG_ERR_HIP;
         }
-        HIPCHK(c, launch_shells(c->cfg.precision, work, M, nbins, scale, c->diag_bins, c->stream));
+        HIPCHK(c, launch_shells(c->cfg.precision, work, M, nbins, comp == 1, c->shell_parts, c->stream));
     }
+    HIPCHK(c, launch_shells_sum(c->shell_parts, M, nbins, scale, c->diag_bins, c->stream));
     HIPCHK(c, hipMemcpyAsync(out, c->diag_bins, nbins * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return DG_OK;

@@ -175,6 +175,7 @@ struct SampleArgs {
     int what;             // 0: the five conserved fields; 1..3: velocity component what-1; 4: statistics
     void *out;            // grid (what 0..3): [field][Z][Y][X] with the pitches below
     long long px, py, pf; // row, plane and field pitches of out, in elements
+    int pair;             // the rows of out allow stores of two elements
     double gamma;
     double lo, hi;        // PDF range of log10(rho); nbins > 0 enables the PDF
     int nbins;
@@ -183,8 +184,12 @@ struct SampleArgs {
 };
 long long sample_blocks(long long nc);
 hipError_t launch_sample(int k, int S, int prec, const SampleArgs &a, const Leg1D &L, hipStream_t s);
-// bins[s] += scale * weight * |c|^2 over an R2C spectrum [M][M][M/2+1] (interleaved complex)
-hipError_t launch_shells(int prec, const void *spec, int M, int nbins, double scale, double *bins, hipStream_t s);
+// shell sums of an R2C spectrum [M][M][M/2+1] (interleaved complex): one share per wave into part
+// (first: written, else added to), then bins[s] = scale * (the shares' sum)
+constexpr long long SHELL_PARTS = 1 << 21;  // doubles of the share buffer: waves x shells
+int shells_waves(int M);
+hipError_t launch_shells(int prec, const void *spec, int M, int nbins, int first, double *part, hipStream_t s);
+hipError_t launch_shells_sum(const double *part, int M, int nbins, double scale, double *bins, hipStream_t s);
 hipError_t launch_fill_zero(unsigned long long *p, long long n, hipStream_t s);
 hipError_t launch_sum_into(const double *p, long long n, double *acc, hipStream_t s);
 hipError_t launch_reset(int k, int prec, void *y, const Leg1D &L, long long nc, int nx, double gm1, double ce,
@@ -409,5 +414,6 @@ struct dg_ctx {
     int fft_m = 0;
     double *diag_bins = nullptr;           // [DIAG_MAX_BINS] shell sums, then [DIAG_MAX_BINS + 2] counts
     double *diag_partials = nullptr;       // per-block Mach sums, then the total
+    double *shell_parts = nullptr;         // per-wave shell sums of the spectrum, made on first use
     std::string err;
 };
