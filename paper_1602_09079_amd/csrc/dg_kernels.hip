@@ -818,48 +818,70 @@ __global__ __launch_bounds__(stage_threads<PREC>()) __attribute__((amdgpu_waves_
 
 // k = 0: one weight per field, and the scheme is first-order Godunov finite volume:
 // R = sum_a (Fhat(q, q_{+a}) - Fhat(q_{-a}, q)) / h_a minus the source at the cell centre (the
-// single Gauss point).  One thread per cell, workgroups of 64 x 4 cells in x and y: each cell
-// solves its +x and +y faces and shares them through LDS with the cell that needs them as its -x
-// or -y face (the same inputs and arithmetic, so the same bits as solving it there); faces on the
-// tile's low edges and the z faces are solved by both of their cells.  No products.
+// single Gauss point).  One thread per cell, workgroups of 64 x 4 cells in x and y that sweep a chunk
+// of z: each cell solves its +x, +y and +z faces, shares the first two through LDS with the cells that
+// need them as their -x or -y face (the same inputs and arithmetic, so the same bits as solving it
+// there) and carries the third to the next plane.  The tile's low faces are solved by wave 0 (the
+// 64 y faces) and by four lanes of wave 1 (the x faces).  No products.
+//
+// What bounds it: memory, 13 values a cell and stage with the driving (256^3 FP32: 0.87 and 1.2 GB, 178
+// and 246 us at the rate of a large copy).  One plane per workgroup in launch order read each cell's
+// z neighbours again on other XCDs and solved every z face twice: 374 us a stage on average; the sweep,
+// in contiguous ranges of tiles per XCD, takes 263.
 constexpr int FV_TX = 64, FV_TY = 4, FV_THREADS = FV_TX * FV_TY;
 
-template <int PREC, bool FORCE, int RS>
+template <int PREC, bool FORCE, int RS, bool BIG>
 __global__ __launch_bounds__(FV_THREADS) void fv_stage_kernel(StageArgs a) {
     using PR = Prec<PREC>;
     using S = typename PR::S;
     using C = typename PR::C;
-    __shared__ C fx[FV_TY][FV_TX][NF], fy[FV_TY][FV_TX][NF];  // each cell's +x and +y face fluxes
+    // +x and +y face fluxes of the tile, and of its low faces, by parity of the plane
+    __shared__ C fx[2][NF][FV_TY][FV_TX + 1], fy[2][NF][FV_TY + 1][FV_TX];
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int tx = threadIdx.x % FV_TX, ty = threadIdx.x / FV_TX;
-    const int ntx = (nx + FV_TX - 1) / FV_TX, nty = (ny + FV_TY - 1) / FV_TY;
-    const long long bid = blockIdx.x;
-    const int bx = (int)(bid % ntx);
-    const long long bzy = bid / ntx;
-    const int by = (int)(bzy % nty), iz = (int)(bzy / nty);
-    const int ix = bx * FV_TX + tx, iy = by * FV_TY + ty;
+    const int ntx = a.nbx, nty = (ny + FV_TY - 1) / FV_TY;
+    long long item;  // in 8 contiguous ranges by workgroup id modulo 8 (one per XCD)
+    {
+        const long long bid = blockIdx.x, lo = a.nitems / 8, extra = a.nitems % 8;
+        const int xcd = (int)(bid & 7);
+        item = (bid >> 3) + xcd * lo + (xcd < extra ? xcd : extra);
+    }
+    const int bx = (int)(item % ntx);
+    const long long bzy = item / ntx;
+    const int by = (int)(bzy % nty), z0 = (int)(bzy / nty) * a.zlen;
+    const int z1 = z0 + a.zlen < nz ? z0 + a.zlen : nz;
+    const int x0 = bx * FV_TX, y0t = by * FV_TY, ix = x0 + tx, iy = y0t + ty;
     const bool act = ix < nx && iy < ny;
     double dtd = a.dt;
     if (a.rate) dtd = a.dtfac / a.rate[0];
     if (a.tacc && blockIdx.x == 0 && threadIdx.x == 0) a.tacc[0] += dtd;
-    const long long row = (long long)iz * ny + iy;
     const S *yin = static_cast<const S *>(a.yin);
-    auto load = [&](int x, int yy, int zz, C q[5]) {
+    // element offsets inside a plane of this thread's cell, its x and y neighbours, and (four lanes of
+    // wave 1) the two cells of the tile's low x face in row tx
+    const unsigned unx = (unsigned)nx;
+    auto at = [&](int x, int yy) -> long long {
         x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
         yy = yy < 0 ? yy + ny : (yy >= ny ? yy - ny : yy);
+        return (long long)yy * NF * nx + x;
+    };
+    const int cxi = ix < nx ? ix : nx - 1, cyi = iy < ny ? iy : ny - 1;
+    const long long oc = at(cxi, cyi), ox = at(cxi + 1, cyi), oy = at(cxi, cyi + 1);
+    const int lrow = y0t + (tx & (FV_TY - 1)) < ny ? y0t + (tx & (FV_TY - 1)) : ny - 1;
+    const long long ol = ty == 0 ? at(cxi, cyi - 1) : at(x0 - 1, lrow), orr = at(x0, lrow);
+    const long long plane = (long long)NF * nx * ny;
+    // the cell at plane offset o of z plane zz (uniform)
+    auto load = [&](long long o, int zz, C q[5]) {
         const S *src = yin;
-        if (a.halo_lo && zz < 0) {  // across the ends of a z slab: the halo planes
+        long long zi = 0;
+        if (a.halo_lo && zz < 0)  // across the ends of a z slab: the halo planes
             src = static_cast<const S *>(a.halo_lo);
-            zz = 0;
-        } else if (a.halo_hi && zz >= nz) {
+        else if (a.halo_hi && zz >= nz)
             src = static_cast<const S *>(a.halo_hi);
-            zz = 0;
-        } else {
-            zz = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
-        }
-        const long long b = ((long long)zz * ny + yy) * NF * nx + x;
+        else
+            zi = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
+        const PlaneView<S, BIG> pv(src, plane, zi, o);
 #pragma unroll
-        for (int i = 0; i < NF; i++) q[i] = (C)src[b + (long long)i * nx];
+        for (int i = 0; i < NF; i++) q[i] = (C)pv.get(i, unx);
     };
     const C gam = (C)a.gamma;
     auto flux = [&](auto axis_c, const C qL[5], const C qR[5], C F[5]) {
@@ -869,99 +891,114 @@ __global__ __launch_bounds__(FV_THREADS) void fv_stage_kernel(StageArgs a) {
         else
             hllc<PR, AX>(qL, qR, gam, F);
     };
-    C q[5] = {1, 0, 0, 0, 1}, R[5] = {0, 0, 0, 0, 0};
-    C Fpx[5], Fpy[5];
-    if (act) {
-        load(ix, iy, iz, q);
-        C qn[5];
-        load(ix + 1, iy, iz, qn);
-        flux(std::integral_constant<int, 0>{}, q, qn, Fpx);
-        load(ix, iy + 1, iz, qn);
-        flux(std::integral_constant<int, 1>{}, q, qn, Fpy);
-#pragma unroll
-        for (int i = 0; i < NF; i++) {
-            fx[ty][tx][i] = Fpx[i];
-            fy[ty][tx][i] = Fpy[i];
-        }
-    }
-    __syncthreads();
-    if (!act) return;
-    C Fmx[5], Fmy[5];
-    if (tx > 0) {  // the -x neighbour is the thread to the left (same row, ix - 1 >= 0)
-#pragma unroll
-        for (int i = 0; i < NF; i++) Fmx[i] = fx[ty][tx - 1][i];
-    } else {
-        C qm[5];
-        load(ix - 1, iy, iz, qm);
-        flux(std::integral_constant<int, 0>{}, qm, q, Fmx);
-    }
-    if (ty > 0) {  // the -y neighbour is the thread below (iy - 1 >= 0)
-#pragma unroll
-        for (int i = 0; i < NF; i++) Fmy[i] = fy[ty - 1][tx][i];
-    } else {
-        C qm[5];
-        load(ix, iy - 1, iz, qm);
-        flux(std::integral_constant<int, 1>{}, qm, q, Fmy);
-    }
-    {
-        const C ih = (C)(1.0 / a.h[0]);
-#pragma unroll
-        for (int i = 0; i < NF; i++) R[i] += (Fpx[i] - Fmx[i]) * ih;
-    }
-    {
-        const C ih = (C)(1.0 / a.h[1]);
-#pragma unroll
-        for (int i = 0; i < NF; i++) R[i] += (Fpy[i] - Fmy[i]) * ih;
-    }
-    {
-        C qm[5], qp[5], Fm[5], Fp[5];
-        load(ix, iy, iz - 1, qm);
-        load(ix, iy, iz + 1, qp);
-        flux(std::integral_constant<int, 2>{}, qm, q, Fm);
-        flux(std::integral_constant<int, 2>{}, q, qp, Fp);
-        const C ih = (C)(1.0 / a.h[2]);
-#pragma unroll
-        for (int i = 0; i < NF; i++) R[i] += (Fp[i] - Fm[i]) * ih;
-    }
-    if constexpr (FORCE) {
-        // the driving acceleration at the cell centre, from the k = 0 cache layout [component][x]
-        const S *ac = static_cast<const S *>(a.acache) + row * (3LL * nx) + ix;
-        C sE = 0;
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            const C av = (C)ac[(long long)c * nx];
-            R[1 + c] -= q[0] * av;
-            sE += q[1 + c] * av;
-        }
-        R[4] -= sE;
-    }
-    S *out = static_cast<S *>(a.out);
-    const S *y0 = static_cast<const S *>(a.y0);
-    const long long b = row * NF * nx + ix;
+    const C ihx = (C)a.ih[0], ihy = (C)a.ih[1], ihz = (C)a.ih[2];
     const C dt = (C)dtd;
+    C q[5] = {1, 0, 0, 0, 1}, qn[5] = {1, 0, 0, 0, 1}, Fm[5] = {0, 0, 0, 0, 0};
+    if (act) {
+        C qm[5];
+        load(oc, z0 - 1, qm);
+        load(oc, z0, q);
+        flux(std::integral_constant<int, 2>{}, qm, q, Fm);
+    }
+    for (int z = z0; z < z1; z++) {
+        const int par = (z - z0) & 1;
+        C Fpx[5], Fpy[5], R[5] = {0, 0, 0, 0, 0};
+        if (act) {
+            C qx[5], qy[5];
+            load(ox, z, qx);
+            load(oy, z, qy);
+            load(oc, z + 1, qn);
+            flux(std::integral_constant<int, 0>{}, q, qx, Fpx);
+            flux(std::integral_constant<int, 1>{}, q, qy, Fpy);
 #pragma unroll
-    for (int i = 0; i < NF; i++) {
-        const long long j = b + (long long)i * nx;
-        if (a.mode == 0) {
-            out[j] = (S)R[i];
-        } else {
-            const C base = (C)a.b * (q[i] - dt * R[i]);
-            out[j] = (S)(a.a != 0.0 ? (C)a.a * (C)y0[j] + base : base);
+            for (int i = 0; i < NF; i++) {
+                fx[par][i][ty][tx + 1] = Fpx[i];
+                fy[par][i][ty + 1][tx] = Fpy[i];
+            }
+            if (ty == 0) {
+                C qm[5], F[5];
+                load(ol, z, qm);
+                flux(std::integral_constant<int, 1>{}, qm, q, F);
+#pragma unroll
+                for (int i = 0; i < NF; i++) fy[par][i][0][tx] = F[i];
+            }
+        }
+        if (ty == 1 && tx < FV_TY && y0t + tx < ny) {  // the tile's low x face in row tx
+            C ql[5], qr[5], F[5];
+            load(ol, z, ql);
+            load(orr, z, qr);
+            flux(std::integral_constant<int, 0>{}, ql, qr, F);
+#pragma unroll
+            for (int i = 0; i < NF; i++) fx[par][i][tx][0] = F[i];
+        }
+        __syncthreads();  // (the other parity's fluxes are read before this barrier's next turn)
+        if (act) {
+            C Fp[5];
+            flux(std::integral_constant<int, 2>{}, q, qn, Fp);
+#pragma unroll
+            for (int i = 0; i < NF; i++) {
+                R[i] += (Fpx[i] - fx[par][i][ty][tx]) * ihx;
+                R[i] += (Fpy[i] - fy[par][i][ty][tx]) * ihy;
+                R[i] += (Fp[i] - Fm[i]) * ihz;
+                Fm[i] = Fp[i];
+            }
+            if constexpr (FORCE) {
+                // the driving acceleration at the cell centre, from the k = 0 cache layout [component][x]
+                const PlaneView<S, BIG> ac(a.acache, 3LL * nx * ny, z, (long long)iy * 3 * nx + ix);
+                C sE = 0;
+#pragma unroll
+                for (int c = 0; c < 3; c++) {
+                    const C av = (C)ac.get(c, unx);
+                    R[1 + c] -= q[0] * av;
+                    sE += q[1 + c] * av;
+                }
+                R[4] -= sE;
+            }
+            const PlaneView<S, BIG> po(a.out, plane, z, oc), p0(a.y0, plane, z, oc);
+            C v0[5] = {0, 0, 0, 0, 0};
+            if (a.mode != 0 && a.a != 0.0) {
+#pragma unroll
+                for (int i = 0; i < NF; i++) v0[i] = (C)p0.get(i, unx);
+            }
+#pragma unroll
+            for (int i = 0; i < NF; i++) {
+                if (a.mode == 0) {
+                    po.put(i, unx, (S)R[i]);
+                } else {
+                    const C base = (C)a.b * (q[i] - dt * R[i]);
+                    po.put(i, unx, (S)(a.a != 0.0 ? (C)a.a * v0[i] + base : base));
+                }
+                q[i] = qn[i];
+            }
         }
     }
 }
 
-template <int PREC>
-static hipError_t launch_fv_t(const StageArgs &a, hipStream_t s) {
-    const long long nb = (long long)((a.nx + FV_TX - 1) / FV_TX) * ((a.ny + FV_TY - 1) / FV_TY) * a.nz;
+template <int PREC, bool BIG>
+static hipError_t launch_fv_b(const StageArgs &a, hipStream_t s) {
+    const dim3 grid((unsigned)a.nitems), block(FV_THREADS);
     if (a.riemann == 1) {
-        if (a.forcing) hipLaunchKernelGGL((fv_stage_kernel<PREC, true, 1>), dim3(nb), dim3(FV_THREADS), 0, s, a);
-        else hipLaunchKernelGGL((fv_stage_kernel<PREC, false, 1>), dim3(nb), dim3(FV_THREADS), 0, s, a);
+        if (a.forcing) hipLaunchKernelGGL((fv_stage_kernel<PREC, true, 1, BIG>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((fv_stage_kernel<PREC, false, 1, BIG>), grid, block, 0, s, a);
     } else {
-        if (a.forcing) hipLaunchKernelGGL((fv_stage_kernel<PREC, true, 0>), dim3(nb), dim3(FV_THREADS), 0, s, a);
-        else hipLaunchKernelGGL((fv_stage_kernel<PREC, false, 0>), dim3(nb), dim3(FV_THREADS), 0, s, a);
+        if (a.forcing) hipLaunchKernelGGL((fv_stage_kernel<PREC, true, 0, BIG>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((fv_stage_kernel<PREC, false, 0, BIG>), grid, block, 0, s, a);
     }
     return hipGetLastError();
+}
+
+template <int PREC>
+static hipError_t launch_fv_t(StageArgs a, hipStream_t s) {
+    // z chunk: the longest of at most 16 planes that still leaves about 2048 workgroups (8 per compute
+    // unit); a chunk pays one z face and one plane of start-up
+    const long long tiles = (long long)((a.nx + FV_TX - 1) / FV_TX) * ((a.ny + FV_TY - 1) / FV_TY);
+    long long zl = tiles * a.nz / 2048;
+    zl = zl < 1 ? 1 : zl > 16 ? 16 : zl;
+    a.zlen = (int)zl;
+    a.nbx = (a.nx + FV_TX - 1) / FV_TX;
+    a.nitems = tiles * ((a.nz + zl - 1) / zl);
+    const bool big = (long long)sizeof(typename Prec<PREC>::S) * NF * a.nx * a.ny >= (1LL << 31);
+    return big ? launch_fv_b<PREC, true>(a, s) : launch_fv_b<PREC, false>(a, s);
 }
 
 template <int K, int PREC>

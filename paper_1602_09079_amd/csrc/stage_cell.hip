@@ -168,14 +168,6 @@ struct CellLds {
     static_assert(RAW + NF * H * 64 <= ELEMS, "the edge cells' weights fit");
 };
 
-// A copy the compiler cannot see through: addresses formed from it are formed where they are used.
-// Without it every address of the sweep is a loop invariant, hoisted, and spilled.
-template <class T>
-__device__ inline T opaque(T v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // a wave-uniform value, in scalar registers
 __device__ inline float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 __device__ inline double uniform(double v) {
@@ -197,55 +189,6 @@ __device__ inline void pin(T (&v)[A][B]) {
 
 // orders this wave's LDS accesses for the compiler; the LDS unit serves a wave in order
 __device__ inline void lds_order() { asm volatile("" ::: "memory"); }
-
-// Access to a state or a plane-wise array: buffer loads with a resource per z plane and 32-bit lane
-// offsets; BIG: planes of 2 GiB and more, 64-bit lane addresses.
-template <class C, bool BIG>
-struct PlaneView {
-    __amdgpu_buffer_rsrc_t rs;
-    const C *p;
-    unsigned off;  // lane offset in bytes
-    __device__ PlaneView(const void *base, long long plane, long long z, long long lane_elem) {
-        const C *b = static_cast<const C *>(base) + z * plane;
-        if constexpr (BIG) {
-            p = b + lane_elem;
-        } else {
-            rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<C *>(b), (short)0,
-                                                   (int)(unsigned)(plane * (long long)sizeof(C)), BUF_DWORD3);
-            off = opaque((unsigned)(lane_elem * (long long)sizeof(C)));
-        }
-    }
-    __device__ C get(unsigned row, unsigned nx) const {  // row: uniform
-        if constexpr (BIG)
-            return p[(long long)row * nx];
-        else
-            return bload(C(), rs, off, row * nx * (unsigned)sizeof(C));
-    }
-    __device__ void put(unsigned row, unsigned nx, C v) const {
-        if constexpr (BIG)
-            const_cast<C *>(p)[(long long)row * nx] = v;
-        else
-            bstore(v, rs, off, row * nx * (unsigned)sizeof(C));
-    }
-    // row `row` of this lane's cell into LDS by the load unit, at dst (FP64: the 64 low words, then the
-    // 64 high words); it counts as a vector memory operation and the compiler does not wait for it
-    __device__ void to_lds(unsigned row, unsigned nx, C *dst) const {
-        if constexpr (BIG) {
-            const C v = p[(long long)row * nx];
-            int *d = reinterpret_cast<int *>(dst) + (threadIdx.x & 63);
-            int u[sizeof(C) / 4];
-            __builtin_memcpy(u, &v, sizeof(C));
-            d[0] = u[0];
-            if (sizeof(C) == 8) d[64] = u[sizeof(C) / 4 - 1];
-        } else {
-#pragma unroll
-            for (int h = 0; h < (int)sizeof(C) / 4; h++)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rs, (__attribute__((address_space(3))) void *)(reinterpret_cast<int *>(dst) + 64 * h), 4, off,
-                    row * nx * (unsigned)sizeof(C) + 4 * h, 0, 0);
-        }
-    }
-};
 
 // a value that to_lds put down: d points at its low word
 __device__ inline float from_lds(const int *d, float) { return __int_as_float(d[0]); }
