@@ -1622,30 +1622,47 @@ __device__ inline long long mean_index(long long cell, int i, int N, int nx) {
     return ((r * NF + i) * N) * nx + (cell - r * nx);
 }
 
-// Grid-stride over the cells with a fixed grid: each thread keeps the largest rate of its cells, the
-// workgroup reduces them (wave shuffles, then LDS), and one atomic max per workgroup goes to the slot
-// (a per-wave atomic on one address serialised ~260k atomics per call at 256^3).
-constexpr int CFL_THREADS = 256, CFL_BLOCKS = 2048;
+// Each workgroup takes items of one run of 1024 cells of a row (several whole rows if they are short), the next one's means requested while this one's
+// rate is formed (so no division by the row length per cell and two rounds of loads in flight); each
+// thread keeps the largest rate of its cells, the workgroup reduces them (wave shuffles, then LDS), and
+// one atomic max per workgroup goes to the slot.  Atomics on one address serialise, so the grid is at
+// most CFL_BLOCKS: 64^3 FP32 6.6 us, 256^3 at k = 0 75 us (2048 workgroups of 256 and a 64-bit division
+// per cell: 14 and 106).
+constexpr int CFL_THREADS = 1024, CFL_BLOCKS = 512;
 
 template <class S>
-__global__ __launch_bounds__(CFL_THREADS) void cfl_kernel(const S *__restrict__ y, int N, int nx, long long nc,
-                                                          double gamma, double hx, double hy, double hz,
+__global__ __launch_bounds__(CFL_THREADS) void cfl_kernel(const S *__restrict__ y, int N, int nx, long long rows,
+                                                          double gamma, double ihx, double ihy, double ihz,
                                                           double *rate_slot, double *zero_slot) {
     __shared__ double wmax[CFL_THREADS / 64];
     double rate = 0.0;
-    for (long long cell = (long long)blockIdx.x * blockDim.x + threadIdx.x; cell < nc;
-         cell += (long long)gridDim.x * blockDim.x) {
-        const double rho = (double)y[mean_index(cell, 0, N, nx)];
-        const double mx = (double)y[mean_index(cell, 1, N, nx)];
-        const double my = (double)y[mean_index(cell, 2, N, nx)];
-        const double mz = (double)y[mean_index(cell, 3, N, nx)];
-        const double E = (double)y[mean_index(cell, 4, N, nx)];
+    const int runs = (nx + CFL_THREADS - 1) / CFL_THREADS;  // runs per row
+    const int pack = runs == 1 ? CFL_THREADS / nx : 1, sub = runs == 1 ? threadIdx.x / nx : 0;  // rows per item
+    const int x0 = threadIdx.x - sub * nx;
+    const long long items = runs == 1 ? (rows + pack - 1) / pack : rows * runs, fs = (long long)N * nx;
+    auto load = [&](long long it, S m[5]) {
+        long long r = runs == 1 ? it * pack + (sub < pack ? sub : 0) : it / runs;
+        const int x = runs == 1 ? x0 : (int)(it - r * runs) * CFL_THREADS + threadIdx.x;
+        if (r >= rows) r = rows - 1;
+        const S *p = y + r * NF * fs + (x < nx ? x : nx - 1);  // threads past the end repeat a cell
+#pragma unroll
+        for (int i = 0; i < NF; i++) m[i] = p[i * fs];
+    };
+    S cur[5], nxt[5];
+    long long it = blockIdx.x;
+    if (it < items) load(it, cur);
+    for (; it < items; it += gridDim.x) {
+        if (it + gridDim.x < items) load(it + gridDim.x, nxt);
+        const double rho = (double)cur[0], mx = (double)cur[1], my = (double)cur[2], mz = (double)cur[3];
+        const double E = (double)cur[4];
         const double inv = 1.0 / rho;
         const double p = (gamma - 1.0) * (E - 0.5 * (mx * mx + my * my + mz * mz) * inv);
         const double c = sqrt(gamma * p * inv);
-        double r = (fabs(mx * inv) + c) / hx + (fabs(my * inv) + c) / hy + (fabs(mz * inv) + c) / hz;
+        double r = (fabs(mx * inv) + c) * ihx + (fabs(my * inv) + c) * ihy + (fabs(mz * inv) + c) * ihz;
         if (!(r >= 0.0)) r = __builtin_inf();  // non-physical cell: force dt -> 0
         rate = fmax(rate, r);
+#pragma unroll
+        for (int i = 0; i < NF; i++) cur[i] = nxt[i];
     }
     rate = wave_max(rate);
     if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = rate;
@@ -1661,14 +1678,16 @@ __global__ __launch_bounds__(CFL_THREADS) void cfl_kernel(const S *__restrict__ 
 
 hipError_t launch_cfl(int prec, const void *y, int N, int nx, long long nc, double gamma, const double h[3],
                       double *rate_slot, double *zero_slot, hipStream_t s) {
-    long long nb = (nc + CFL_THREADS - 1) / CFL_THREADS;
+    const long long rows = nc / nx;
+    const int pack = nx <= CFL_THREADS ? CFL_THREADS / nx : 1;
+    long long nb = pack > 1 ? (rows + pack - 1) / pack : rows * ((nx + CFL_THREADS - 1) / CFL_THREADS);
     if (nb > CFL_BLOCKS) nb = CFL_BLOCKS;
     if (prec == DG_FP64)
-        hipLaunchKernelGGL((cfl_kernel<double>), dim3(nb), dim3(CFL_THREADS), 0, s, (const double *)y, N, nx, nc, gamma,
-                           h[0], h[1], h[2], rate_slot, zero_slot);
+        hipLaunchKernelGGL((cfl_kernel<double>), dim3(nb), dim3(CFL_THREADS), 0, s, (const double *)y, N, nx, rows, gamma,
+                           1.0 / h[0], 1.0 / h[1], 1.0 / h[2], rate_slot, zero_slot);
     else
-        hipLaunchKernelGGL((cfl_kernel<float>), dim3(nb), dim3(CFL_THREADS), 0, s, (const float *)y, N, nx, nc, gamma,
-                           h[0], h[1], h[2], rate_slot, zero_slot);
+        hipLaunchKernelGGL((cfl_kernel<float>), dim3(nb), dim3(CFL_THREADS), 0, s, (const float *)y, N, nx, rows, gamma,
+                           1.0 / h[0], 1.0 / h[1], 1.0 / h[2], rate_slot, zero_slot);
     return hipGetLastError();
 }
 
