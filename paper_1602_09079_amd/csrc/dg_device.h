@@ -49,6 +49,25 @@ struct Dims {
     static constexpr int P = n * n;
 };
 
+// FP64 reciprocal and square root of the pointwise physics: the hardware estimate refined by two
+// Newton steps (and, for the root, two corrections of the result), about half of the instructions of
+// the correctly rounded sequences, which also rescale operands this physics does not meet.
+__device__ inline double rcp64(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
+__device__ inline double sqrt64(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    return x == 0.0 ? x : g;
+}
+
 // ------------------------------------------------------------------ precision policies
 //
 // S: storage type; C: pointwise arithmetic; Acc: MFMA accumulator.
@@ -74,8 +93,8 @@ struct Prec<DG_FP64> {
     __device__ static int orow(int g, int r) { return g + 4 * r; }
     __device__ static BF mkb(const C *v) { return BF{v[0]}; }
     __device__ static BF2 mkb2(const C *v) { return BF{v[0]}; }
-    __device__ static C rcp(C x) { return 1.0 / x; }
-    __device__ static C sqrt_(C x) { return __builtin_sqrt(x); }
+    __device__ static C rcp(C x) { return rcp64(x); }
+    __device__ static C sqrt_(C x) { return sqrt64(x); }
 };
 
 template <>

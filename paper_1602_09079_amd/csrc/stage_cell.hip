@@ -111,35 +111,6 @@ constexpr int face_field(int f) {
     return f == 0 || f == 4 ? f : f == 1 ? 1 + AX : f == 2 ? (AX == 0 ? 2 : 1) : (AX == 2 ? 2 : 3);
 }
 
-// Reciprocal and square root of the pointwise physics.  FP64: the hardware estimate refined by two
-// Newton steps (and, for the root, one correction of the result), about half of the instructions of
-// the correctly rounded sequences, which also rescale operands this physics does not meet.
-template <class C>
-struct CellMath;
-template <>
-struct CellMath<float> {
-    __device__ static float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-    __device__ static float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
-};
-template <>
-struct CellMath<double> {
-    __device__ static double rcp(double x) {
-        double y = __builtin_amdgcn_rcp(x);
-        y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-        return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-    }
-    __device__ static double sqrt_(double x) {
-        const double y = __builtin_amdgcn_rsq(x);
-        double g = x * y, h = 0.5 * y;
-        const double r = __builtin_fma(-h, g, 0.5);
-        g = __builtin_fma(g, r, g);
-        h = __builtin_fma(h, r, h);
-        g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
-        g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
-        return x == 0.0 ? x : g;
-    }
-};
-
 __device__ inline float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ inline double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -218,15 +189,11 @@ struct CellSplit {
 template <int K, class C, bool FORCE, int RS, bool BIG, bool SPLIT>
 __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     using L = Leg<K>;
-    using M = CellMath<C>;
+    using PR = Prec<sizeof(C) == 8 ? DG_FP64 : DG_FP32>;
     using LD = CellLds<K>;
     constexpr int N = Dims<K>::N, n = K + 1, P = Dims<K>::P, NT = LD::NT, NV = LD::NV;
     constexpr int NL = K * (K + 1) * (K + 2) / 6;  // modes of degree <= k - 1
     constexpr ModeTab<K> T;
-    struct PR {
-        __device__ static C rcp(C x) { return M::rcp(x); }
-        __device__ static C sqrt_(C x) { return M::sqrt_(x); }
-    };
     extern __shared__ __attribute__((aligned(16))) char lds_all[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     C *const lds0 = reinterpret_cast<C *>(lds_all);
@@ -317,7 +284,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         C q[NF];
 #pragma unroll
         for (int f = 0; f < NF; f++) q[f] = w[face_field<AX>(f)][0];
-        const C inv = M::rcp(q[0]), u = q[1] * inv;
+        const C inv = PR::rcp(q[0]), u = q[1] * inv;
         const C p = g1 * (q[4] - C(0.5) * ((q[1] * q[1] + q[2] * q[2] + q[3] * q[3]) * inv));
         F[0] = q[1];
         F[1] = q[1] * u + p;
@@ -607,7 +574,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             for (int l = 0; l < NL; l++) mu[j][l] = C(0);
         C fb[9];
         {
-            const C inv = M::rcp(w[0][0]);
+            const C inv = PR::rcp(w[0][0]);
             const C u = w[1][0] * inv, v = w[2][0] * inv, ww = w[3][0] * inv;
             const C p = g1 * (w[4][0] - C(0.5) * (w[1][0] * u + w[2][0] * v + w[3][0] * ww));
             const C ep = w[4][0] + p;
@@ -697,7 +664,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                             if (L::P[ww][qc] != 0.0) s = fma_((C)L::P[ww][qc], Z[i][ww], s);
                         q[i] = s;
                     }
-                    const C inv = M::rcp(q[0]);
+                    const C inv = PR::rcp(q[0]);
                     const C u = q[1] * inv, v = q[2] * inv, ww = q[3] * inv;
                     const C p = g1 * (q[4] - C(0.5) * (q[1] * u + q[2] * v + q[3] * ww));
                     const C ep = q[4] + p;

@@ -38,6 +38,17 @@
 
 namespace dgmi {
 
+// The pointwise physics of this kernel.  FP64 keeps the correctly rounded quotient and root: with the
+// shorter sequences of Prec<DG_FP64> the compiler (ROCm 7.2) fails on the exact solver's variant.
+template <int PREC>
+struct K4Prec : Prec<PREC> {};
+template <>
+struct K4Prec<DG_FP64> : Prec<DG_FP64> {
+    __device__ static double rcp(double x) { return 1.0 / x; }
+    __device__ static double sqrt_(double x) { return __builtin_sqrt(x); }
+};
+
+
 namespace {
 
 constexpr int K4_NM = 35, K4_E = NF * K4_NM;
@@ -83,7 +94,7 @@ __global__ __launch_bounds__(k4_threads(PREC))
 __attribute__((amdgpu_waves_per_eu(PREC == DG_FP64 ? 1 : 2, PREC == DG_FP64 ? 1 : 2))) void stage_k4_kernel(StageArgs a) {
     constexpr bool F64 = PREC == DG_FP64;
     constexpr int THREADS = k4_threads(PREC);
-    using PR = Prec<PREC>;
+    using PR = K4Prec<PREC>;
     using C = typename PR::C;
     using Acc = typename PR::Acc;
     constexpr int ESZ = sizeof(C);
