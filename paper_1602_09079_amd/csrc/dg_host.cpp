@@ -1158,8 +1158,7 @@ dg_status dg_set_forcing(dg_ctx *c, int32_t nmodes, const int32_t *nvec, const d
     }
     if (!c->fmodes) HIPCHK(c, hipMalloc(&c->fmodes, t.size() * sizeof(double)));
     if (!c->acache)
-        HIPCHK(c, hipMalloc(&c->acache, (size_t)accel_slab_elems(c->cfg.k, c->cfg.n[0], c->cell) * c->cfg.n[1] * c->cfg.n[2] *
-                                            elem_bytes(c)));
+        HIPCHK(c, hipMalloc(&c->acache, (size_t)accel_elems(c->cfg.k, c->cfg.n, c->cell) * elem_bytes(c)));
     HIPCHK(c, hipMemcpyAsync(c->fmodes, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
     GaussNodes xg{};
     double wg[5];

@@ -145,12 +145,15 @@ TableLayout make_layout(int k, int prec);
 struct GaussNodes {
     double x[5];
 };
-// elements of the driving acceleration cache per (z, y) row of cells: 3 components x 16 ceil(Q/16) points x nx
-// (k = 0 and the one-cell-per-lane kernel: [component][point][x], Q points)
-inline long long accel_slab_elems(int k, int nx, bool cell) {
-    if (k == 0 || cell) return 3LL * (k + 1) * (k + 1) * (k + 1) * nx;
+// elements of the driving acceleration cache: 3 components x 16 ceil(Q/16) points of every cell;
+// k = 0: the cell centre only; the one-cell-per-lane kernel: whole tiles of 64 cells, Q points
+constexpr int CELL_TILE = 8;  // cells per wave of that kernel along x and along y
+inline long long accel_elems(int k, const int32_t n[3], bool cell) {
     const int Q = (k + 1) * (k + 1) * (k + 1);
-    return (long long)((Q + 15) / 16) * 16 * 3 * nx;
+    const long long nx = n[0], ny = n[1], nz = n[2];
+    if (cell)
+        return (nx + CELL_TILE - 1) / CELL_TILE * ((ny + CELL_TILE - 1) / CELL_TILE) * nz * 3 * Q * CELL_TILE * CELL_TILE;
+    return (k == 0 ? 3LL : (long long)((Q + 15) / 16) * 16 * 3) * nx * ny * nz;
 }
 constexpr double LIMIT_EPS = 1e-13;  // minimum density and pressure of the positivity limiter
 // FP32 storage: the targets are raised to 2^-20 times the cell's mean density / (gamma-1) x mean energy
@@ -243,7 +246,6 @@ hipError_t launch_stage_k3(int prec, const StageArgs &a, int grid, int lds_bytes
 hipError_t set_stage_k3_attributes(int prec, int lds_bytes);
 hipError_t stage_k3_occupancy(int prec, int lds_bytes, int *per_cu);
 // the one-cell-per-lane kernel of k = 1, 2 in FP64 and FP32 (stage_cell.hip)
-constexpr int CELL_TILE = 8;  // cells per wave along x and along y
 constexpr int CELL_WAVES = 4; // waves per workgroup: consecutive tiles along x
 hipError_t launch_stage_cell(int k, int prec, const StageArgs &a, hipStream_t s);
 hipError_t stage_cell_setup(int k, int prec, int *per_cu);

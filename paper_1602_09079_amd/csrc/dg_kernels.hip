@@ -1173,8 +1173,8 @@ __global__ __launch_bounds__(ACC_THREADS) void accel_cache_kernel(const double *
     constexpr bool F64 = sizeof(S) == 8;
     __shared__ double P[MAX_FORCING_MODES][3][2];
     const long long items = (long long)ny * nz * n * n;
-    const bool rows = K == 0 || cell;
-    const long long aslab = rows ? 3LL * Q * nx : (long long)RT1 * 16 * 3 * nx;
+    const long long aslab = K == 0 ? 3LL * nx : (long long)RT1 * 16 * 3 * nx;
+    const int ntx = (nx + CELL_TILE - 1) / CELL_TILE, nty = (ny + CELL_TILE - 1) / CELL_TILE;
     for (long long it = blockIdx.x; it < items; it += gridDim.x) {
         const long long row = it / (n * n);
         const int qbc = (int)(it - row * (n * n)), qb = qbc % n, qc = qbc / n;
@@ -1212,9 +1212,16 @@ __global__ __launch_bounds__(ACC_THREADS) void accel_cache_kernel(const double *
                 for (int c = 0; c < 3; c++) acc[c] += P[m][c][0] * er - P[m][c][1] * ei;
             }
             const int rho = qa + n * qb + n * n * qc;
-            if (rows) {  // [component][point][x]
+            if constexpr (K == 0) {  // [component][x]
 #pragma unroll
-                for (int c = 0; c < 3; c++) orow[(long long)(c * Q + rho) * nx + ix] = (S)acc[c];
+                for (int c = 0; c < 3; c++) orow[(long long)c * nx + ix] = (S)acc[c];
+                continue;
+            }
+            if (cell) {  // the one-cell-per-lane kernel: [z][tile][component][point][cell of the tile]
+                const long long tile = ((long long)iz * nty + iy / CELL_TILE) * ntx + ix / CELL_TILE;
+                const int ln = iy % CELL_TILE * CELL_TILE + ix % CELL_TILE;
+#pragma unroll
+                for (int c = 0; c < 3; c++) out[(tile * (3 * Q) + c * Q + rho) * 64 + ln] = (S)acc[c];
                 continue;
             }
             const int t = rho / 16, rr = rho % 16;
@@ -1222,7 +1229,7 @@ __global__ __launch_bounds__(ACC_THREADS) void accel_cache_kernel(const double *
 #pragma unroll
             for (int c = 0; c < 3; c++) orow[(((long long)(t * 3 + c) * 4 + g) * nx + ix) * 4 + r] = (S)acc[c];
         }
-        if (!rows && qbc == 0 && RT1 * 16 > Q) {  // the padding rows of the last tile
+        if (K > 0 && !cell && qbc == 0 && RT1 * 16 > Q) {  // the padding rows of the last tile
             for (int j = threadIdx.x; j < (RT1 * 16 - Q) * nx; j += ACC_THREADS) {
                 const int rho = Q + j / nx, ix = j % nx;
                 const int t = rho / 16, rr = rho % 16;

@@ -588,16 +588,17 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             fb[7] = ep * v;
             fb[8] = ep * ww;
         }
-        // driving acceleration at the points of a column, requested two columns ahead
-        const long long aplane = 3LL * n * n * n * nx * ny;
+        // driving acceleration at the points of a column, requested two columns ahead; the cache holds a
+        // tile's 64 values of a point together, so a read is two whole cache lines
         C ac[3][3][n];
         auto accel = [&](int col, C o[3][n]) {
-            const PlaneView<C, BIG> av(a.acache, aplane, z, (long long)iy * 3 * n * n * n * nx + ix);
+            constexpr int AR = 3 * n * n * n;
+            const PlaneView<C, BIG> av(a.acache, AR * 64, (long long)z * ntx * nty + by * ntx + bx, lane);
             const int qa = col / n, qb = col % n;
 #pragma unroll
             for (int c = 0; c < 3; c++)
 #pragma unroll
-                for (int qc = 0; qc < n; qc++) o[c][qc] = av.get(c * n * n * n + (qc * n + qb) * n + qa, unx);
+                for (int qc = 0; qc < n; qc++) o[c][qc] = av.get(c * n * n * n + (qc * n + qb) * n + qa, 64);
         };
         if constexpr (FORCE) {
             accel(A0 * n, ac[(A0 * n) % 3]);
@@ -923,8 +924,7 @@ constexpr int split_lds() { return CellSplit<K, C>::ELEMS * (int)sizeof(C); }
 template <int K, class C, bool FORCE, int RS>
 static hipError_t launch_cell_t(const StageArgs &a, hipStream_t s) {
     const long long plane = (long long)sizeof(C) * NF * Dims<K>::N * a.nx * a.ny;
-    const long long aplane = (long long)sizeof(C) * 3 * Dims<K>::Q * a.nx * a.ny;
-    const bool big = plane >= (1LL << 31) || (FORCE && aplane >= (1LL << 31));
+    const bool big = plane >= (1LL << 31);
     if (a.wgw == 0) {  // one tile and plane per workgroup, split by task (small meshes, so never big planes)
         if (big) return hipErrorInvalidValue;
         hipLaunchKernelGGL((cell_split_kernel<K, C, FORCE, RS>), dim3((unsigned)a.nitems),
