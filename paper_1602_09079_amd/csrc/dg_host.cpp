@@ -503,7 +503,7 @@ hipError_t stage_occupancy(int k, int prec, int lds_bytes, int *blocks_per_cu);
 
 // x-blocks per row of cells and y rows per work item of the context's stage kernel
 static int stage_nbx(const dg_ctx *c) {
-    const int b = c->cell ? CELL_TILE : c->k3x ? K3_BLK : BLK_INNER;
+    const int b = c->cell ? CELL_TX : c->k3x ? K3_BLK : BLK_INNER;
     return (c->cfg.n[0] + b - 1) / b;
 }
 // Whether the one-cell-per-lane kernel splits each tile and plane over several waves by task: where the
@@ -513,9 +513,9 @@ static int stage_nbx(const dg_ctx *c) {
 // The two forms round differently, so the rule looks at the plane only: a z slab takes the same one as
 // the whole mesh, and the z chunk length does not enter.
 static bool stage_split(const dg_ctx *c) {
-    return ((c->cfg.n[0] + CELL_TILE - 1) / CELL_TILE) * (long long)((c->cfg.n[1] + CELL_TILE - 1) / CELL_TILE) <= 16;
+    return ((c->cfg.n[0] + CELL_TX - 1) / CELL_TX) * (long long)((c->cfg.n[1] + CELL_TY - 1) / CELL_TY) <= 16;
 }
-static int stage_rows(const dg_ctx *c) { return c->cell ? CELL_TILE : stage_rows_per_item(c->cfg.precision); }
+static int stage_rows(const dg_ctx *c) { return c->cell ? CELL_TY : stage_rows_per_item(c->cfg.precision); }
 
 // ====================================================================== ABI
 
@@ -874,7 +874,7 @@ dg_status run_stage(dg_ctx *c, const void *y0, const void *yin, void *out, doubl
     if (c->cell) {
         if (stage_split(c)) {
             s.wgw = 0;
-            s.nitems = (long long)s.nbx * ((s.ny + CELL_TILE - 1) / CELL_TILE) * s.nz;
+            s.nitems = (long long)s.nbx * ((s.ny + CELL_TY - 1) / CELL_TY) * s.nz;
         } else {
             // a mesh that cannot fill the chip with workgroups of four waves gives each wave a workgroup
             s.wgw = s.nitems <= 1024 ? 1 : CELL_WAVES;

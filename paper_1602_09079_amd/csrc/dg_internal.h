@@ -147,12 +147,12 @@ struct GaussNodes {
 };
 // elements of the driving acceleration cache: 3 components x 16 ceil(Q/16) points of every cell;
 // k = 0: the cell centre only; the one-cell-per-lane kernel: whole tiles of 64 cells, Q points
-constexpr int CELL_TILE = 8;  // cells per wave of that kernel along x and along y
+constexpr int CELL_TX = 16, CELL_TY = 4;  // cells per wave of that kernel along x and along y
 inline long long accel_elems(int k, const int32_t n[3], bool cell) {
     const int Q = (k + 1) * (k + 1) * (k + 1);
     const long long nx = n[0], ny = n[1], nz = n[2];
     if (cell)
-        return (nx + CELL_TILE - 1) / CELL_TILE * ((ny + CELL_TILE - 1) / CELL_TILE) * nz * 3 * Q * CELL_TILE * CELL_TILE;
+        return (nx + CELL_TX - 1) / CELL_TX * ((ny + CELL_TY - 1) / CELL_TY) * nz * 3 * Q * CELL_TX * CELL_TY;
     return (k == 0 ? 3LL : (long long)((Q + 15) / 16) * 16 * 3) * nx * ny * nz;
 }
 constexpr double LIMIT_EPS = 1e-13;  // minimum density and pressure of the positivity limiter

@@ -1174,7 +1174,7 @@ __global__ __launch_bounds__(ACC_THREADS) void accel_cache_kernel(const double *
     __shared__ double P[MAX_FORCING_MODES][3][2];
     const long long items = (long long)ny * nz * n * n;
     const long long aslab = K == 0 ? 3LL * nx : (long long)RT1 * 16 * 3 * nx;
-    const int ntx = (nx + CELL_TILE - 1) / CELL_TILE, nty = (ny + CELL_TILE - 1) / CELL_TILE;
+    const int ntx = (nx + CELL_TX - 1) / CELL_TX, nty = (ny + CELL_TY - 1) / CELL_TY;
     for (long long it = blockIdx.x; it < items; it += gridDim.x) {
         const long long row = it / (n * n);
         const int qbc = (int)(it - row * (n * n)), qb = qbc % n, qc = qbc / n;
@@ -1218,8 +1218,8 @@ __global__ __launch_bounds__(ACC_THREADS) void accel_cache_kernel(const double *
                 continue;
             }
             if (cell) {  // the one-cell-per-lane kernel: [z][tile][component][point][cell of the tile]
-                const long long tile = ((long long)iz * nty + iy / CELL_TILE) * ntx + ix / CELL_TILE;
-                const int ln = iy % CELL_TILE * CELL_TILE + ix % CELL_TILE;
+                const long long tile = ((long long)iz * nty + iy / CELL_TY) * ntx + ix / CELL_TX;
+                const int ln = iy % CELL_TY * CELL_TX + ix % CELL_TX;
 #pragma unroll
                 for (int c = 0; c < 3; c++) out[(tile * (3 * Q) + c * Q + rho) * 64 + ln] = (S)acc[c];
                 continue;

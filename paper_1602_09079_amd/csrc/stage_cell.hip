@@ -12,10 +12,10 @@
 // by groups of 8 rows leave more of a ragged mesh idle than 8 x 8 tiles).  k = 2 FP32 at 64^3 issues
 // vector instructions 56% of the time with two waves per SIMD; the rest is memory and LDS latency.
 //
-// A wave owns a tile of 8 x 8 cells in x and y and sweeps a chunk of z.  Waves are independent:
+// A wave owns a tile of 16 x 4 cells in x and y and sweeps a chunk of z.  Waves are independent:
 // nothing is shared between them, so there is no barrier, and a small mesh is cut into as many work
 // items as it has tiles and chunks.  Four waves on consecutive tiles along x form a workgroup, so the
-// 32-byte runs of a row that they read come from the same cache lines of one compute unit (k = 2 FP32
+// 64-byte runs of a row that they read come from the same cache lines of one compute unit (k = 2 FP32
 // at 64^3: 133 -> 124 us against one wave per workgroup).
 //
 // Small meshes (cell_split_kernel): with a few waves in flight the time of a launch is one wave's chain
@@ -33,7 +33,7 @@
 // Faces.  A face is described by its 2D trace modes (p, q), p + q <= k, of each field: 15 values at
 // k = 1, 30 at k = 2 instead of 20 or 45 point values.  Neighbours exchange trace modes and flux
 // moments in LDS.  Each lane solves its +x, +y and +z faces; the faces on the tile's low x and y
-// edges (16 of them) are solved point by point, spread over all 64 lanes.  The +z flux moments are
+// edges (20 of them) are solved point by point, spread over all 64 lanes.  The +z flux moments are
 // carried to the next plane.  Every solve takes the same arithmetic on the same modes, so a face on
 // a tile edge, which two waves solve, gets the same flux in both.
 //
@@ -116,28 +116,31 @@ __device__ inline double fma_(double a, double b, double c) { return __builtin_f
 
 // ------------------------------------------------------------------ LDS of a wave
 //
-// Exchange planes, one per (field, 2D mode): 8 rows of 13 slots; a row is a line of cells along the
-// axis exchanged.  Slots 0..7: the tile's cells; 8, 9: the trace modes of the cells past the high x
-// and y edges; 10, 11: the flux moments of the low x and y edges.  An odd row pitch spreads the rows
-// over the banks.  Then one region that first holds the 16 low-edge faces (both sides' trace modes and
-// their point fluxes) and after them the cells' own trace modes on the face being solved.
-constexpr int CT = CELL_TILE;  // tile edge
-constexpr int CX_ROW = 13, CX_PLANE = CT * CX_ROW;
+// Exchange planes, one per (field, 2D mode): 64 slots of the tile's cells (slot = lane), then the trace
+// modes past the high x edge (4) and below the low x edge's flux moments (4), and the same of the y
+// edges (16 and 16).  Then one region that first holds the trace modes of the 20 low-edge faces from
+// both sides and after them the cells' own trace modes on the face being solved.  The low-edge faces'
+// point fluxes pass through the cells' slots of the planes, which are free at that time.
+constexpr int CTX = CELL_TX, CTY = CELL_TY;  // the tile
+constexpr int EF = CTX + CTY;                // its low-edge faces: CTY in x, then CTX in y
+constexpr int SL_XHI = 64, SL_XLO = SL_XHI + CTY, SL_YHI = SL_XLO + CTY, SL_YLO = SL_YHI + CTX;
+constexpr int CX_PLANE = SL_YLO + CTX;
 template <int K>
 struct CellLds {
-    static constexpr int NT = (K + 1) * (K + 2) / 2, NV = NF * NT, P = Dims<K>::P;
+    static constexpr int NT = (K + 1) * (K + 2) / 2, NV = NF * NT, P = Dims<K>::P, N = Dims<K>::N;
     static constexpr int X = NV * CX_PLANE;         // exchange planes
-    static constexpr int E = 2 * NV * 2 * CT;       // low-edge trace modes [side][value][face]
-    static constexpr int F = NF * 2 * CT * P;       // low-edge point fluxes [field][face point]
+    static constexpr int E = 2 * NV * EF;           // low-edge trace modes [side][value][face]
     static constexpr int S = NV * 64;               // this tile's trace modes on the face being solved
-    // during the volume integral: the weights (k = 2, to free their registers), and the weights of the
-    // 32 cells across the tile's edges on their way in from memory
-    static constexpr bool STASH = K >= 2;
-    static constexpr int N = Dims<K>::N, W = STASH ? NF * N * 64 : 0;
-    static constexpr int RAW = X > W ? X : W, H = N / 2;
-    static constexpr int ELEMS = X + (E + F > S ? E + F : S);
-    static_assert(RAW + NF * H * 64 <= ELEMS, "the edge cells' weights fit");
+    // during the volume integral: the weights but two (k = 2, to free their registers), and the weights
+    // of the 40 cells across the tile's edges on their way in from memory: 32 past the y edges
+    // (two lanes a cell, half of the modes each), then 8 past the x edges (eight values a load)
+    static constexpr int STASHED = K >= 2 ? NF * N - 2 : 0, W = STASHED * 64, H = N / 2;
+    static constexpr int RAW = W, RAWN = NF * H * 64 + (NF * N + 7) / 8 * 64;
+    static constexpr int ELEMS0 = X + (E > S ? E : S), ELEMS = ELEMS0 > RAW + RAWN ? ELEMS0 : RAW + RAWN;
+    static_assert(NF * EF * P <= 64 * NV, "the point fluxes fit the cells' slots");
 };
+// point flux number j of the low-edge faces among the cells' slots
+__device__ inline int flux_slot(int j) { return (j >> 6) * CX_PLANE + (j & 63); }
 
 // a wave-uniform value, in scalar registers
 __device__ inline float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
@@ -198,9 +201,9 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     C *const lds0 = reinterpret_cast<C *>(lds_all);
     C *const lds = lds0 + (SPLIT ? CellSplit<K, C>::base(wave) : wave * LD::ELEMS);
-    C *const lx = lds, *const le = lds + LD::X, *const lf = le + LD::E;
+    C *const lx = lds, *const le = lds + LD::X;
 
-    const int lane = threadIdx.x & 63, cx = lane & 7, cy = lane >> 3;
+    const int lane = threadIdx.x & 63, cx = lane & (CTX - 1), cy = lane / CTX;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const unsigned unx = (unsigned)nx;
     // items in 8 contiguous ranges by workgroup id modulo 8 (one per XCD), so neighbouring tiles share
@@ -214,11 +217,11 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         item = ((bid >> 3) + xcd * lo + (xcd < extra ? xcd : extra)) * per + (SPLIT ? 0 : wave);
     }
     if (item >= a.nitems) return;
-    const int ntx = a.nbx, nty = (ny + CT - 1) / CT;
+    const int ntx = a.nbx, nty = (ny + CTY - 1) / CTY;
     const int bx = (int)(item % ntx);
     const long long rest = item / ntx;
     const int by = (int)(rest % nty), zc = (int)(rest / nty);
-    const int x0 = bx * CT, y0t = by * CT;
+    const int x0 = bx * CTX, y0t = by * CTY;
     const int zlen = SPLIT ? 1 : a.zlen;
     const int z0 = zc * zlen, z1 = z0 + zlen < nz ? z0 + zlen : nz;
     // lanes past the end of a ragged tile take the cells the periodic mesh continues with
@@ -226,13 +229,14 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     const bool keep = x0 + cx < nx && y0t + cy < ny;
     const long long plane = (long long)NF * N * nx * ny;
     const long long cell = (long long)iy * NF * N * nx + ix;
-    // edge cell of lanes 0..31 (and again of 32..63): low x, high x, low y, high y
-    long long ecell;
+    // the cells across the edges: past the y edges lanes 0..15 low, 16..31 high (32..63 again), past the
+    // x edges lanes 0..3 low, 4..7 high (8..63 again)
+    long long ycell, xcell;
     {
-        const int eg = (lane >> 3) & 3, ej = lane & 7;
-        const int ex = eg == 0 ? (x0 + nx - 1) % nx : eg == 1 ? (x0 + CT) % nx : (x0 + ej) % nx;
-        const int ey = eg == 2 ? (y0t + ny - 1) % ny : eg == 3 ? (y0t + CT) % ny : (y0t + ej) % ny;
-        ecell = (long long)ey * NF * N * nx + ex;
+        const int ex = (x0 + cx) % nx, ey = (lane & CTX) ? (y0t + CTY) % ny : (y0t + ny - 1) % ny;
+        ycell = (long long)ey * NF * N * nx + ex;
+        const int fx = (lane & CTY) ? (x0 + CTX) % nx : (x0 + nx - 1) % nx, fy = (y0t + (lane & (CTY - 1))) % ny;
+        xcell = (long long)fy * NF * N * nx + fx;
     }
     const C *yin = static_cast<const C *>(a.yin);
     // z plane zz of the input, across the ends from the halo planes or periodic
@@ -408,49 +412,58 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     using PLUS = std::integral_constant<int, 1>;
     using MINUS = std::integral_constant<int, -1>;
 
-    // the weights of the 32 cells across the tile's edges (lanes 0..31: low x, high x, low y, high y;
-    // lanes 32..63 take the second half of the modes), requested before the volume integral
+    // the weights of the 40 cells across the tile's edges, requested before the volume integral
     auto request_edges = [&](int z) {
         const int el = opaque(lane);
-        const PlaneView<C, BIG> pv(yin, plane, z, ecell + (long long)(el >> 5) * LD::H * nx);
+        const PlaneView<C, BIG> py(yin, plane, z, ycell + (long long)(el >> 5) * LD::H * nx);
         C *dst = lds + LD::RAW;
         asm volatile("" : "+s"(dst));
 #pragma unroll
         for (int i = 0; i < NF; i++)
 #pragma unroll
-            for (int l = 0; l < LD::H; l++) pv.to_lds(i * N + l, unx, dst + (i * LD::H + l) * 64);
+            for (int l = 0; l < LD::H; l++) py.to_lds(i * N + l, unx, dst + (i * LD::H + l) * 64);
+        const PlaneView<C, BIG> px(yin, plane, z, xcell + (long long)(el >> 3) * nx);
+        dst += NF * LD::H * 64;
+#pragma unroll
+        for (int r = 0; r < NF * N / 8; r++) px.to_lds(8 * r, unx, dst + r * 64);
+        if ((NF * N) % 8 != 0 && el < (NF * N) % 8 * 8) px.to_lds(NF * N / 8 * 8, unx, dst + NF * N / 8 * 64);
     };
-    // trace modes of the edge cells and of the tile's own low-edge cells, then the fluxes of the 16
+    // trace modes of the edge cells and of the tile's own low-edge cells, then the fluxes of the 20
     // low-edge faces and their moments
     auto edges = [&](int z) {
-        const int ol = opaque(lane), cx = ol & 7, cy = ol >> 3;
+        const int ol = opaque(lane), cx = ol & (CTX - 1), cy = ol / CTX;
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the edge cells have landed
         lds_order();
-        C ew[NF][N];  // (lanes 32..63 read the same cells and drop them)
-        {
-            const bool ay = ol & (2 * CT);  // normal axis y
-            const int *src = reinterpret_cast<const int *>(lds + LD::RAW);
-            int mo[N];  // word offset of the mode with degrees (r, p, q) as seen from the face
-#pragma unroll
-            for (int l = 0; l < N; l++) {  // (r, p, q) = (u, v, w) of the x faces
-                const int ly = face_mode<K, 1>(T.u[l], T.v[l], T.w[l]);
-                constexpr int WD = sizeof(C) / 4 * 64;
-                const int ax_ = (l % LD::H) * WD + (l >= LD::H ? 32 : 0), ay_ = (ly % LD::H) * WD + (ly >= LD::H ? 32 : 0);
-                mo[l] = (ol & 31) + (ay ? ay_ : ax_);
-            }
+        // lanes 0..31 take the y edges' cells, 32..39 the x edges' (the others read along and drop them);
+        // a mode is read as seen from the face, with degrees (r, p, q)
+        const bool ay = ol < 2 * CTX;
+        constexpr int WD = sizeof(C) / 4 * 64;  // words of a load
+        const int *const raw = reinterpret_cast<const int *>(lds + LD::RAW);
+        C ew[NF][N];
+        if (ay) {
 #pragma unroll
             for (int i = 0; i < NF; i++)
 #pragma unroll
-                for (int l = 0; l < N; l++)
-                    ew[i][l] = from_lds(src + i * LD::H * (int)(sizeof(C) / 4) * 64 + mo[l], C());
+                for (int l = 0; l < N; l++) {
+                    const int ly = face_mode<K, 1>(T.u[l], T.v[l], T.w[l]);
+                    ew[i][l] = from_lds(raw + ol + (i * LD::H + ly % LD::H) * WD + (ly >= LD::H ? 32 : 0), C());
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NF; i++)
+#pragma unroll
+                for (int l = 0; l < N; l++) {
+                    const int val = i * N + l;
+                    ew[i][l] = from_lds(raw + (ol & 7) + (NF * LD::H + val / 8) * WD + val % 8 * 8, C());
+                }
         }
         lds_order();
-        if (ol < 4 * CT) {
-            const int eg = ol >> 3, ej = ol & 7;
-            const bool ay = eg >= 2;  // normal axis y
-            const C sg = (eg & 1) ? C(-1) : C(1);
-            const int stride = (eg & 1) ? CX_PLANE : 2 * CT;
-            const int d0 = opaque((eg & 1) ? ej * CX_ROW + CT + (ay ? 1 : 0) : LD::X + (ay ? CT : 0) + ej);
+        if (ol < 2 * CTX + 2 * CTY) {
+            const bool hi = ay ? ol >= CTX : ol >= 2 * CTX + CTY;
+            const int j = ay ? cx : ol & (CTY - 1);
+            const C sg = hi ? C(-1) : C(1);
+            const int stride = hi ? CX_PLANE : EF;
+            const int d0 = opaque(hi ? (ay ? SL_YHI : SL_XHI) + j : LD::X + (ay ? CTY : 0) + j);
             C c1[n];
 #pragma unroll
             for (int r = 0; r <= K; r++) c1[r] = (r & 1) ? sg * (C)L::E[r] : (C)L::E[r];
@@ -472,13 +485,13 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         {
             C t[NF][NT];
             trace(I0{}, MINUS{}, t);
-            if (cx == 0) put_modes(le + opaque(NV * 2 * CT + cy), 2 * CT, t);
+            if (cx == 0) put_modes(le + opaque(NV * EF + cy), EF, t);
             trace(I1{}, MINUS{}, t);
-            if (cy == 0) put_modes(le + opaque(NV * 2 * CT + CT + cx), 2 * CT, t);
+            if (cy == 0) put_modes(le + opaque(NV * EF + CTY + cx), EF, t);
         }
         lds_order();
 #pragma unroll 1
-        for (int e = opaque(lane); e < 2 * CT * P; e += 64) {
+        for (int e = opaque(lane); e < EF * P; e += 64) {
             const int fc = e / P, pt = e - fc * P, b = pt / n, c = pt - b * n;
             C pb[n], pc[n], qL[NF], qR[NF], F[NF];
             pb[0] = pc[0] = C(1);
@@ -490,19 +503,19 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
 #pragma unroll
             for (int f = 0; f < NF; f++) {
                 C o[n];
-                row_of(le + f * NT * 2 * CT + fc, 2 * CT, pb, o);
+                row_of(le + f * NT * EF + fc, EF, pb, o);
                 qL[f] = point_of(o, pc);
-                row_of(le + (NV + f * NT) * 2 * CT + fc, 2 * CT, pb, o);
+                row_of(le + (NV + f * NT) * EF + fc, EF, pb, o);
                 qR[f] = point_of(o, pc);
             }
             solve(qL, qR, F);
 #pragma unroll
-            for (int f = 0; f < NF; f++) lf[f * 2 * CT * P + e] = F[f];
+            for (int f = 0; f < NF; f++) lx[flux_slot(f * EF * P + e)] = F[f];
         }
         lds_order();
 #pragma unroll 1
-        for (int e = opaque(lane); e < 2 * CT * NF; e += 64) {  // (face, field)
-            const int f = e / (2 * CT), fc = e - f * 2 * CT;
+        for (int e = opaque(lane); e < EF * NF; e += 64) {  // (face, field)
+            const int f = e / EF, fc = e - f * EF;
             C m[NT];
 #pragma unroll
             for (int t = 0; t < NT; t++) m[t] = C(0);
@@ -516,14 +529,14 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                 }
 #pragma unroll
                 for (int c = 0; c < n; c++) {
-                    const C d = lf[f * 2 * CT * P + fc * P + b * n + c];
+                    const C d = lx[flux_slot((f * EF + fc) * P + b * n + c)];
 #pragma unroll
                     for (int q = 0; q <= K; q++)
                         if (L::P[q][c] != 0.0) s[q] = fma_((C)(L::W[c] * L::P[q][c]), d, s[q]);
                 }
                 add_row(m, s, (C)L::W[b], pb);
             }
-            C *dst = lx + f * NT * CX_PLANE + (fc & 7) * CX_ROW + (fc >= CT ? 11 : 10);
+            C *dst = lx + f * NT * CX_PLANE + (fc < CTY ? SL_XLO + fc : SL_YLO + fc - CTY);
 #pragma unroll
             for (int t = 0; t < NT; t++) dst[t * CX_PLANE] = m[t];
         }
@@ -532,27 +545,29 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     // the +x or +y face of every lane; both of its cells take the moments
     auto side = [&](auto ax_c) {
         constexpr int AX = decltype(ax_c)::value;
-        const int ol = opaque(lane), me = AX == 0 ? ol & 7 : ol >> 3, ln = AX == 0 ? ol >> 3 : ol & 7;
-        C *const row = lx + ln * CX_ROW;
+        const int ol = opaque(lane), sx = ol & (CTX - 1), sy = ol / CTX;
+        // slots of the cell above, of this one, and of the moments from below
+        const int up = AX == 0 ? (sx == CTX - 1 ? SL_XHI + sy : ol + 1) : (sy == CTY - 1 ? SL_YHI + sx : ol + CTX);
+        const int down = AX == 0 ? (sx == 0 ? SL_XLO + sy : ol - 1) : (sy == 0 ? SL_YLO + sx : ol - CTX);
         C F0[NF], m[NF][NT];
         {
             C t[NF][NT];
             trace(ax_c, MINUS{}, t);
-            put_modes(row + me, CX_PLANE, t);
+            put_modes(lx + ol, CX_PLANE, t);
             trace(ax_c, PLUS{}, t);
             put_modes(le + opaque(lane), 64, t);
         }
         lds_order();
         mean_flux(ax_c, F0);
-        face(le + opaque(lane), row + (me == CT - 1 ? CT + AX : me + 1), std::integral_constant<int, CX_PLANE>{}, F0, m);
+        face(le + ol, lx + up, std::integral_constant<int, CX_PLANE>{}, F0, m);
         lift(ax_c, PLUS{}, m);
         lds_order();
         // the moments as absolute fluxes for the cell above
 #pragma unroll
         for (int f = 0; f < NF; f++) m[f][0] += F0[f];
-        put_modes(row + me, CX_PLANE, m);
+        put_modes(lx + ol, CX_PLANE, m);
         lds_order();
-        const C *src = row + (me == 0 ? 10 + AX : me - 1);
+        const C *src = lx + down;
 #pragma unroll
         for (int f = 0; f < NF; f++)
 #pragma unroll
@@ -566,7 +581,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     // volume integral and driving source of the Gauss planes A0 <= qa < A1 along x
     auto volume = [&](int z, auto a0_c, auto a1_c) {
         constexpr int A0 = decltype(a0_c)::value, A1 = decltype(a1_c)::value;
-        constexpr bool STASH = LD::STASH && !SPLIT;
+        constexpr int STASHED = SPLIT ? 0 : LD::STASHED;
         C mu[9][NL];  // moments of the fluxes xx xy xz yy yz zz of the momentum, x y z of the energy
 #pragma unroll
         for (int j = 0; j < 9; j++)
@@ -604,16 +619,17 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             accel(A0 * n, ac[(A0 * n) % 3]);
             accel(A0 * n + 1, ac[(A0 * n + 1) % 3]);
         }
-        if constexpr (STASH) {
+        if constexpr (STASHED > 0) {
             lds_order();
             C *const wp = lds + opaque(lane);
 #pragma unroll
             for (int i = 0; i < NF; i++)
 #pragma unroll
-                for (int l = 0; l < N; l++) wp[(i * N + l) * 64] = w[i][l];
+                for (int l = 0; l < N; l++)
+                    if (i * N + l < STASHED) wp[(i * N + l) * 64] = w[i][l];
             lds_order();
         }
-        const C *const ws = lds + opaque(lane);  // the weights' copies (STASH)
+        const C *const ws = lds + opaque(lane);  // the weights' copies
 #pragma unroll
         for (int qa = A0; qa < A1; qa++) {
             C Mx[NF][NT];
@@ -623,7 +639,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                 for (int v = 0; v <= K; v++)
 #pragma unroll
                     for (int ww = 0; ww <= K - v; ww++) {
-                        auto wt = [&](int l) { return STASH ? ws[(i * N + l) * 64] : w[i][l]; };
+                        auto wt = [&](int l) { return i * N + l < STASHED ? ws[(i * N + l) * 64] : w[i][l]; };
                         C s = wt(mode_of<K>(0, v, ww));
 #pragma unroll
                         for (int u = 1; u <= K - v - ww; u++)
@@ -721,12 +737,13 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                 pin(mu);
             }
         }
-        if constexpr (STASH) {
+        if constexpr (STASHED > 0) {
             lds_order();
 #pragma unroll
             for (int i = 0; i < NF; i++)
 #pragma unroll
-                for (int l = 0; l < N; l++) w[i][l] = ws[(i * N + l) * 64];
+                for (int l = 0; l < N; l++)
+                    if (i * N + l < STASHED) w[i][l] = ws[(i * N + l) * 64];
         }
         // R_l -= 2/h_a sum over l' of d(l, l') mu_l', l' = l with a lower degree of the other parity along
         // axis a: d = sqrt((2u+1)(2u'+1)); the mass flux's moments are the momentum's modes (mode 0 is the
