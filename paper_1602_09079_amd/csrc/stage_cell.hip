@@ -7,22 +7,27 @@
 // instructions and waits for its exchanges besides.  Here every lane works on a cell of its own and
 // no row is padding.
 //
-// Measured, one driven stage, us, matrix form -> this one: 64^3 k = 1 FP32 168 -> 31, FP64 217 -> 67;
-// k = 2 FP32 233 -> 124, FP64 455 -> 262; a 90 x 77 x 51 mesh at k = 2 FP32 707 -> 197 (14-cell blocks
-// by groups of 8 rows leave more of a ragged mesh idle than 8 x 8 tiles).  k = 2 FP32 at 64^3 issues
-// vector instructions 56% of the time with two waves per SIMD; the rest is memory and LDS latency.
+// Measured, one driven stage, us, matrix form -> this one: 64^3 k = 1 FP32 168 -> 29, FP64 217 -> 66;
+// k = 2 FP32 233 -> 113, FP64 455 -> 261; a 90 x 77 x 51 mesh at k = 2 FP32 707 -> 185 (14-cell blocks
+// by groups of 8 rows leave more of a ragged mesh idle than tiles).  k = 2 FP32 at 64^3 issues vector
+// instructions a little over half of the time with two waves per SIMD; the rest is memory and LDS
+// latency.
 //
 // A wave owns a tile of 16 x 4 cells in x and y and sweeps a chunk of z.  Waves are independent:
 // nothing is shared between them, so there is no barrier, and a small mesh is cut into as many work
 // items as it has tiles and chunks.  Four waves on consecutive tiles along x form a workgroup, so the
 // 64-byte runs of a row that they read come from the same cache lines of one compute unit (k = 2 FP32
-// at 64^3: 133 -> 124 us against one wave per workgroup).
+// at 64^3, by 8 x 8 tiles: 133 -> 124 us against one wave per workgroup).  Tiles of 8 x 8 read 32-byte
+// runs and have twice the cells past their x edges, each of whose values costs a cache line (k = 2 FP32,
+// 8 x 8 -> 16 x 4: 64^3 121 -> 113 us, 128^3 984 -> 885; 12 x 5 or 32 x 2 leave lanes idle or have
+// more edge faces).
 //
 // Small meshes (cell_split_kernel): with a few waves in flight the time of a launch is one wave's chain
 // of dependent instructions and memory round trips.  There a workgroup takes one tile and one plane
 // and its waves one task each - x faces, y faces, the two z faces, the volume integral - and their
-// shares of R are added through LDS in a fixed order (16^3: k = 1 FP64 14.9 -> 8.8 us, k = 2 FP32
-// 30.4 -> 13.5, FP64 47.9 -> 19.3).
+// shares of R are added through LDS in a fixed order (16^3: k = 1 FP64 14.9 -> 8.4 us, k = 2 FP32
+// 30.4 -> 13.7, FP64 47.9 -> 19.0; the waves of the x and the y faces each solve only the tile's
+// low-edge faces of their own axis, 9.8 -> 8.4 us at k = 1 FP64 against all 20 in both).
 //
 // Volume integral.  The integral of F_a against the gradient of the basis needs the moments of F_a
 // with the polynomials of degree k - 1 only: 1 moment at k = 1, 4 at k = 2, of the 9 distinct
@@ -411,17 +416,22 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     using I2 = std::integral_constant<int, 2>;
     using PLUS = std::integral_constant<int, 1>;
     using MINUS = std::integral_constant<int, -1>;
+    using YES = std::true_type;
+    using NO = std::false_type;
 
     // the weights of the 40 cells across the tile's edges, requested before the volume integral
-    auto request_edges = [&](int z) {
+    // (DX, DY: those of the x, the y faces)
+    auto request_edges = [&](int z, auto dx_c, auto dy_c) {
+        constexpr bool DX = decltype(dx_c)::value, DY = decltype(dy_c)::value;
         const int el = opaque(lane);
         const PlaneView<C, BIG> py(yin, plane, z, ycell + (long long)(el >> 5) * LD::H * nx);
         C *dst = lds + LD::RAW;
         asm volatile("" : "+s"(dst));
 #pragma unroll
-        for (int i = 0; i < NF; i++)
+        for (int i = 0; DY && i < NF; i++)
 #pragma unroll
             for (int l = 0; l < LD::H; l++) py.to_lds(i * N + l, unx, dst + (i * LD::H + l) * 64);
+        if constexpr (!DX) return;
         const PlaneView<C, BIG> px(yin, plane, z, xcell + (long long)(el >> 3) * nx);
         dst += NF * LD::H * 64;
 #pragma unroll
@@ -430,13 +440,16 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     };
     // trace modes of the edge cells and of the tile's own low-edge cells, then the fluxes of the 20
     // low-edge faces and their moments
-    auto edges = [&](int z) {
+    auto edges = [&](int z, auto dx_c, auto dy_c) {
+        constexpr bool DX = decltype(dx_c)::value, DY = decltype(dy_c)::value;
+        constexpr int FC0 = DX ? 0 : CTY, NFC = (DX ? CTY : 0) + (DY ? CTX : 0);  // first and number of low-edge faces
+        constexpr int LX = DY ? 2 * CTX : 0;                                     // first lane of the x edges' cells
         const int ol = opaque(lane), cx = ol & (CTX - 1), cy = ol / CTX;
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the edge cells have landed
         lds_order();
         // lanes 0..31 take the y edges' cells, 32..39 the x edges' (the others read along and drop them);
         // a mode is read as seen from the face, with degrees (r, p, q)
-        const bool ay = ol < 2 * CTX;
+        const bool ay = DY && (!DX || ol < LX);
         constexpr int WD = sizeof(C) / 4 * 64;  // words of a load
         const int *const raw = reinterpret_cast<const int *>(lds + LD::RAW);
         C ew[NF][N];
@@ -458,8 +471,8 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                 }
         }
         lds_order();
-        if (ol < 2 * CTX + 2 * CTY) {
-            const bool hi = ay ? ol >= CTX : ol >= 2 * CTX + CTY;
+        if (ol < LX + (DX ? 2 * CTY : 0)) {
+            const bool hi = ay ? ol >= CTX : ol >= LX + CTY;
             const int j = ay ? cx : ol & (CTY - 1);
             const C sg = hi ? C(-1) : C(1);
             const int stride = hi ? CX_PLANE : EF;
@@ -484,14 +497,14 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         }
         {
             C t[NF][NT];
-            trace(I0{}, MINUS{}, t);
-            if (cx == 0) put_modes(le + opaque(NV * EF + cy), EF, t);
-            trace(I1{}, MINUS{}, t);
-            if (cy == 0) put_modes(le + opaque(NV * EF + CTY + cx), EF, t);
+            if constexpr (DX) trace(I0{}, MINUS{}, t);
+            if (DX && cx == 0) put_modes(le + opaque(NV * EF + cy), EF, t);
+            if constexpr (DY) trace(I1{}, MINUS{}, t);
+            if (DY && cy == 0) put_modes(le + opaque(NV * EF + CTY + cx), EF, t);
         }
         lds_order();
 #pragma unroll 1
-        for (int e = opaque(lane); e < EF * P; e += 64) {
+        for (int e = opaque(FC0 * P + lane); e < (FC0 + NFC) * P; e += 64) {
             const int fc = e / P, pt = e - fc * P, b = pt / n, c = pt - b * n;
             C pb[n], pc[n], qL[NF], qR[NF], F[NF];
             pb[0] = pc[0] = C(1);
@@ -514,8 +527,8 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         }
         lds_order();
 #pragma unroll 1
-        for (int e = opaque(lane); e < EF * NF; e += 64) {  // (face, field)
-            const int f = e / EF, fc = e - f * EF;
+        for (int e = opaque(lane); e < NFC * NF; e += 64) {  // (face, field)
+            const int f = e / NFC, fc = FC0 + e - f * NFC;
             C m[NT];
 #pragma unroll
             for (int t = 0; t < NT; t++) m[t] = C(0);
@@ -848,14 +861,19 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     if constexpr (SPLIT) {
         using SP = CellSplit<K, C>;
         if (wave < 2) {
-            request_edges(z0);
+            if (wave == 0)
+                request_edges(z0, YES{}, NO{});
+            else
+                request_edges(z0, NO{}, YES{});
             load_cells(z0);
             clear();
-            edges(z0);
-            if (wave == 0)
+            if (wave == 0) {
+                edges(z0, YES{}, NO{});
                 side(I0{});
-            else
+            } else {
+                edges(z0, NO{}, YES{});
                 side(I1{});
+            }
         } else if (wave == 2) {
             load_cells(z0 - 1);
             zface(z0 - 1, F0);
@@ -906,10 +924,10 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             clear();
             lift(I2{}, MINUS{}, mz);
             pin(R);
-            request_edges(z);
+            request_edges(z, YES{}, YES{});
             volume(z, I0{}, std::integral_constant<int, n>{});
             pin(R);
-            edges(z);
+            edges(z, YES{}, YES{});
             side(I0{});
             side(I1{});
             zface(z, F0);
