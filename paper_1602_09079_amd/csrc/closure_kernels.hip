@@ -27,12 +27,8 @@ namespace dgmi {
 
 typedef float f4c __attribute__((ext_vector_type(4)));
 
-// closure inference: 8 waves per workgroup; the weight fragments in LDS (floats)
-constexpr int CL_THREADS = 512;
-constexpr int CL_W1F = 8 * 35 * 64;     // layer 1: 8 output tiles x 35 K steps
-constexpr int CL_W2F = 8 * 4 * 8 * 64;  // layer 2: 32 K steps x 8 output tiles
-constexpr int CL_W3F = 8 * 4 * 2 * 64;  // layer 3: 32 K steps x 2 output tiles (rows 20..31 zero)
-constexpr int CL_LDS = (CL_W1F + CL_W2F + CL_W3F) * 4;
+constexpr int CL_THREADS = 512;  // inference: 8 waves per workgroup
+constexpr int CL_LDS = CL_IMAGE * 4;
 
 __device__ inline f4c mfma4(float a, float b, f4c c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
@@ -46,12 +42,18 @@ __device__ inline float tanh_act(float x) {
 
 // ------------------------------------------------------------------ inference
 
-// A persistent grid of one 8-wave workgroup per compute unit: the workgroup
-// first copies the three weight matrices into LDS in the order the MFMA A
-// operand takes them (a fragment of 64 floats per K step and output tile,
-// lane l at position l: conflict-free 4-byte reads), 151 KB, then each wave
-// takes groups of 16 consecutive cells in turn.  Read from L2 for every group
-// instead, the weights cost about 600 loads per group and wave.
+// A persistent grid of one 8-wave workgroup per compute unit: the workgroup first copies the network
+// into LDS (156 KB, laid out on the host when the closure is set: closure_image), then each wave takes
+// groups of 16 consecutive cells in turn.  Read from L2 for every group instead, the weights cost about
+// 600 loads per group and wave.
+//
+// Bound by the FP32 matrix cores: 600 products of 32 cycles per group, 128 us at 64^3.  So everything
+// else is placed between them: the eight weights of a step are read (two 16-byte reads) while the
+// products of the step before run, and so are a hidden unit's bias and tanh, the standardising of the
+// features and the loads of the next group's.  64^3 per launch: 283 us with row-major weights gathered
+// by every workgroup, one 4-byte read per product right before it, the activations between the layers
+// and fences at the end; 235 us in this order, 208 us without the fences, of which 16 are start and end.
+// With the loops over K steps rolled up, a third of the code: 247 against 235 us.
 //
 // A wave evaluates 16 consecutive cells (the MFMA columns).  MFMA lane
 // layout (16x16x4, FP32): lane l feeds A[l%16][l/16] and B[l/16][l%16] and
@@ -65,26 +67,8 @@ __device__ inline float tanh_act(float x) {
 //    field 4 (lane group 0).
 template <class S>
 __global__ __launch_bounds__(CL_THREADS) void closure_kernel(ClosureArgs a) {
-    extern __shared__ float wl[];
-    {
-        const float *W1 = a.params;
-        const float *W2 = W1 + CL_NH * CL_NIN + CL_NH;
-        const float *W3 = W2 + CL_NH * CL_NH + CL_NH;
-        for (int e = threadIdx.x; e < CL_W1F; e += CL_THREADS) {  // [t][s][lane]
-            const int l = e & 63, s = (e >> 6) % 35, t = (e >> 6) / 35;
-            wl[e] = W1[(16 * t + (l & 15)) * CL_NIN + 4 * s + (l >> 4)];
-        }
-        for (int e = threadIdx.x; e < CL_W2F; e += CL_THREADS) {  // [t][r][u][lane]
-            const int l = e & 63, u = (e >> 6) & 7, r = (e >> 9) & 3, t = e >> 11;
-            wl[CL_W1F + e] = W2[(16 * u + (l & 15)) * CL_NH + 16 * t + 4 * (l >> 4) + r];
-        }
-        for (int e = threadIdx.x; e < CL_W3F; e += CL_THREADS) {  // [t][r][tile][lane], rows past 20 zero
-            const int l = e & 63, tile = (e >> 6) & 1, r = (e >> 7) & 3, t = e >> 9;
-            const int row = 16 * tile + (l & 15);
-            wl[CL_W1F + CL_W2F + e] = row < CL_NOUT ? W3[row * CL_NH + 16 * t + 4 * (l >> 4) + r] : 0.0f;
-        }
-        __syncthreads();
-    }
+    // (no static LDS beside it, which would shift this block off the 16-byte alignment of its reads)
+    extern __shared__ __align__(16) float wl[];
     const int lane = threadIdx.x & 63;
     const int col = lane & 15;
     const int g = lane >> 4;
@@ -94,7 +78,7 @@ __global__ __launch_bounds__(CL_THREADS) void closure_kernel(ClosureArgs a) {
     const long long slabn = (long long)CL_ROWS * nx;  // 5 fields x 4 modes rows per slab
     const S *y = reinterpret_cast<const S *>(a.y);
     // offsets of the 7 cells whose weights are this lane's features in task w (column col)
-    auto task_bases = [&](long long w, long long base[7]) {
+    auto task_bases = [&](long long w, long long (&base)[7]) {
         const long long c0 = w * 16;
         const long long cell = c0 + col < a.ncells ? c0 + col : a.ncells - 1;
         const int x = (int)(cell % nx);
@@ -115,86 +99,115 @@ __global__ __launch_bounds__(CL_THREADS) void closure_kernel(ClosureArgs a) {
         base[5] = at(0, 0, -1);
         base[6] = at(0, 0, 1);
     };
-    // the raw features of task w (value s: field s % 5, mode g, of cell s / 5 of the 7), requested
-    // one task ahead, after the layer that used the previous ones
-    float fv[35];
-    auto load_feat = [&](long long w) {
-        long long bs[7];
-        task_bases(w, bs);
-    #pragma unroll
-        for (int s = 0; s < 35; s++) fv[s] = (float)y[bs[s / 5] + (long long)((s % 5) * 4 + g) * nx];
-    };
+    // raw feature s of the task with these bases: field s % 5, mode g, of cell s / 5 of the 7
+    auto feature = [&](const long long (&bs)[7], int s) { return (float)y[bs[s / 5] + (long long)((s % 5) * 4 + g) * nx]; };
     const long long wstride = (long long)gridDim.x * (CL_THREADS / 64);
-    long long wave0 = (long long)blockIdx.x * (CL_THREADS / 64) + (threadIdx.x >> 6);
-    if (wave0 < ntasks) load_feat(wave0);
+    const long long wave0 = (long long)blockIdx.x * (CL_THREADS / 64) + (threadIdx.x >> 6);
+    float fv[35];
+    long long base[7];  // of the task whose features fv holds
+    task_bases(wave0 < ntasks ? wave0 : ntasks - 1, base);
+#pragma unroll
+    for (int s = 0; s < 35; s++) fv[s] = feature(base, s);
+    {
+        const f4c *src = reinterpret_cast<const f4c *>(a.image);
+        f4c *dst = reinterpret_cast<f4c *>(wl);
+#pragma unroll
+        for (int i = 0; i < CL_IMAGE / 4 / CL_THREADS; i++) dst[i * CL_THREADS + threadIdx.x] = src[i * CL_THREADS + threadIdx.x];
+        constexpr int e0 = CL_IMAGE / 4 / CL_THREADS * CL_THREADS;
+        if (e0 + threadIdx.x < CL_IMAGE / 4) dst[e0 + threadIdx.x] = src[e0 + threadIdx.x];
+        __syncthreads();
+    }
     for (long long wave = wave0; wave < ntasks; wave += wstride) {
-        const long long cell0 = wave * 16;
-        const bool live = cell0 + col < a.ncells;
-        long long base[7];
-        task_bases(wave, base);
-        const float *b1 = a.params + CL_NH * CL_NIN;
-        const float *b2 = b1 + CL_NH + CL_NH * CL_NH;
-        const float *b3 = b2 + CL_NH + CL_NOUT * CL_NH;
-        // the fragments at this lane: an opaque lane base plus immediate offsets (not a register per
-        // fragment hoisted out of the loop)
-        int lb = lane;
-        asm volatile("" : "+v"(lb));
-        const float *w1l = wl + lb, *w2l = wl + CL_W1F + lb, *w3l = wl + CL_W1F + CL_W2F + lb;
+        const bool live = wave * 16 + col < a.ncells;
+        const long long out0 = base[0];
+        // the network at this lane: opaque bases plus immediate offsets (not a register per fragment
+        // hoisted out of the loop); an LDS offset reaches 64 KB, so one base per 25 steps
+        int l0 = lane, l1 = lane + 25 * 128, l2 = lane + 50 * 128, gb = g;
+        asm volatile("" : "+v"(l0), "+v"(l1), "+v"(l2), "+v"(gb));
+        const f4c *const w4 = reinterpret_cast<const f4c *>(wl);
+        const f4c *const wb[3] = {w4 + l0, w4 + l1, w4 + l2};
+        const float2 *const fn = reinterpret_cast<const float2 *>(wl + CL_FN) + gb;
+        const f4c *const b1 = reinterpret_cast<const f4c *>(wl + CL_B1) + gb;
+        const f4c *const b2 = reinterpret_cast<const f4c *>(wl + CL_B2) + gb;
+        const float *const ob = wl + CL_OUT;  // bias, scale, bound of the outputs
+        f4c fr[2][2];                         // the weights of a step and of the next
+        auto fetch = [&](int st) {
+            fr[st & 1][0] = wb[st / 25][st % 25 * 128];
+            fr[st & 1][1] = wb[st / 25][st % 25 * 128 + 64];
+        };
+        // a step's products; `beside` runs next to them
+        auto step = [&](int st, float b, f4c (&acc)[8], auto beside) {
+            if (st + 1 < CL_STEPS) fetch(st + 1);
+            __builtin_amdgcn_sched_barrier(0);  // (the compiler otherwise moves the reads to their use)
+#pragma unroll
+            for (int j = 0; j < 8; j++) acc[j] = mfma4(fr[st & 1][j >> 2][j & 3], b, acc[j]);
+            beside();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        fetch(0);
 
         // layer 1: 140 -> 128
-        f4c h1[8];
-    #pragma unroll
-        for (int t = 0; t < 8; t++) h1[t] = f4c{0, 0, 0, 0};
-    #pragma unroll
+        f4c h1[8], h2[8], bias[2];
+#pragma unroll
+        for (int t = 0; t < 8; t++) h1[t] = h2[t] = f4c{0, 0, 0, 0};
+        float2 ms[2] = {fn[0], fn[4]};
+        float b = (fv[0] - ms[0].x) * ms[0].y;
+#pragma unroll
         for (int s = 0; s < 35; s++) {
-            const int f = 4 * s + g;
-            const float b = (fv[s] - a.fmean[f]) * a.fistd[f];
-    #pragma unroll
-            for (int t = 0; t < 8; t++) h1[t] = mfma4(w1l[(t * 35 + s) * 64], b, h1[t]);
+            float bn = 0.0f;
+            step(s, b, h1, [&] {
+                if (s + 1 < 35) bn = (fv[s + 1] - ms[(s + 1) & 1].x) * ms[(s + 1) & 1].y;
+                if (s + 2 < 35) ms[s & 1] = fn[4 * (s + 2)];
+                if (s == 33) bias[0] = b1[0];
+                if (s == 34) bias[1] = b1[4];
+            });
+            b = bn;
         }
-    #pragma unroll
+        auto act = [&](f4c &h, const f4c &bs, int r) { h[r] = tanh_act(h[r] + bs[r]); };
+#pragma unroll
+        for (int r = 0; r < 4; r++) act(h1[0], bias[0], r);
+        task_bases(wave + wstride < ntasks ? wave + wstride : ntasks - 1, base);
+        // layer 2: 128 -> 128; beside it the activations of the next four units, and the features of the
+        // next task
+#pragma unroll
         for (int t = 0; t < 8; t++)
-    #pragma unroll
-            for (int r = 0; r < 4; r++) h1[t][r] = tanh_act(h1[t][r] + b1[16 * t + 4 * g + r]);
-
-        asm volatile("" ::: "memory");
-        if (wave + wstride < ntasks) load_feat(wave + wstride);
-        asm volatile("" ::: "memory");
-        // layer 2: 128 -> 128
-        f4c h2[8];
-    #pragma unroll
-        for (int t = 0; t < 8; t++) h2[t] = f4c{0, 0, 0, 0};
-    #pragma unroll
-        for (int t = 0; t < 8; t++)
-    #pragma unroll
-            for (int r = 0; r < 4; r++) {
-    #pragma unroll
-                for (int u = 0; u < 8; u++) h2[u] = mfma4(w2l[((t * 4 + r) * 8 + u) * 64], h1[t][r], h2[u]);
-            }
-    #pragma unroll
-        for (int t = 0; t < 8; t++)
-    #pragma unroll
-            for (int r = 0; r < 4; r++) h2[t][r] = tanh_act(h2[t][r] + b2[16 * t + 4 * g + r]);
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                step(35 + 4 * t + r, h1[t][r], h2, [&] {
+                    fv[4 * t + r] = feature(base, 4 * t + r);
+                    if (t < 7) act(h1[t + 1], bias[(t + 1) & 1], r);
+                    if (r == 0) bias[t & 1] = t < 6 ? b1[4 * (t + 2)] : b2[4 * (t - 6)];
+                });
+#pragma unroll
+        for (int r = 0; r < 4; r++) act(h2[0], bias[0], r);
 
         // layer 3: 128 -> 20 (rows 20..31 of tile 1 are zero)
         f4c o[2] = {f4c{0, 0, 0, 0}, f4c{0, 0, 0, 0}};
-    #pragma unroll
-        for (int t = 0; t < 8; t++)
-    #pragma unroll
+#pragma unroll
+        for (int t = 0; t < 8; t++) {
+            const int st = 35 + 32 + t;
+            if (st + 1 < CL_STEPS) fetch(st + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (t < 3) fv[32 + t] = feature(base, 32 + t);
+#pragma unroll
             for (int r = 0; r < 4; r++) {
-                o[0] = mfma4(w3l[((t * 4 + r) * 2) * 64], h2[t][r], o[0]);
-                o[1] = mfma4(w3l[((t * 4 + r) * 2 + 1) * 64], h2[t][r], o[1]);
+                o[0] = mfma4(fr[st & 1][r >> 1][2 * (r & 1)], h2[t][r], o[0]);
+                o[1] = mfma4(fr[st & 1][r >> 1][2 * (r & 1) + 1], h2[t][r], o[1]);
+                if (t < 7) act(h2[t + 1], bias[(t + 1) & 1], r);
             }
+            if (t < 6) bias[t & 1] = b2[4 * (t + 2)];
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // output entries held by this lane: tile 0 rows 4g+r (field g), tile 1 rows 16+r (lane group 0)
         bool bad = false;
-    #pragma unroll
+#pragma unroll
         for (int r = 0; r < 4; r++) {
             const int j0 = 4 * g + r;
-            o[0][r] += b3[j0];
-            bad |= !(__builtin_fabsf(o[0][r]) <= a.obound[j0]);  // also true for NaN
+            o[0][r] += ob[j0];
+            bad |= !(__builtin_fabsf(o[0][r]) <= ob[2 * CL_NOUT + j0]);  // also true for NaN
             if (g == 0) {
-                o[1][r] += b3[16 + r];
-                bad |= !(__builtin_fabsf(o[1][r]) <= a.obound[16 + r]);
+                o[1][r] += ob[16 + r];
+                bad |= !(__builtin_fabsf(o[1][r]) <= ob[2 * CL_NOUT + 16 + r]);
             }
         }
         // a cell falls back if any of its 20 outputs is out of range: OR over the 4 lane groups
@@ -204,20 +217,20 @@ __global__ __launch_bounds__(CL_THREADS) void closure_kernel(ClosureArgs a) {
         bad = bi != 0;
         S *corr = reinterpret_cast<S *>(a.corr);
         double m0 = 0.0, m4 = 0.0;  // this lane's mean-row corrections (field g; field 4 on group 0)
-    #pragma unroll
+#pragma unroll
         for (int r = 0; r < 4; r++) {
             const int j0 = 4 * g + r;
-            const float c0 = bad ? 0.0f : a.oscale[j0] * o[0][r];
-            if (live) corr[base[0] + (long long)j0 * nx] = (S)c0;
+            const float c0 = bad ? 0.0f : ob[CL_NOUT + j0] * o[0][r];
+            if (live) corr[out0 + (long long)j0 * nx] = (S)c0;
             if (r == 0) m0 = live ? (double)(S)c0 : 0.0;
             if (g == 0) {
-                const float c1 = bad ? 0.0f : a.oscale[16 + r] * o[1][r];
-                if (live) corr[base[0] + (long long)(16 + r) * nx] = (S)c1;
+                const float c1 = bad ? 0.0f : ob[CL_NOUT + 16 + r] * o[1][r];
+                if (live) corr[out0 + (long long)(16 + r) * nx] = (S)c1;
                 if (r == 0) m4 = live ? (double)(S)c1 : 0.0;
             }
         }
         // per-wave sums of the mean rows over the 16 columns, fixed order
-    #pragma unroll
+#pragma unroll
         for (int off = 8; off >= 1; off >>= 1) {
             m0 += __shfl_xor(m0, off, 16);
             m4 += __shfl_xor(m4, off, 16);
@@ -228,33 +241,43 @@ __global__ __launch_bounds__(CL_THREADS) void closure_kernel(ClosureArgs a) {
         if (lane == 0 && fb) atomicAdd(a.fallbacks, (unsigned long long)__popcll(fb));
     }
     // one partial per wave of the grid; the last workgroup to finish forms the means from them in a
-    // fixed order (and resets the counter for the next launch), so no second kernel is launched
+    // fixed order (and resets the counter for the next launch), so no second kernel is launched.  The
+    // partials are exchanged where the counter is counted, past the caches, and their old values awaited
+    // before it is: a __threadfence instead writes the whole L2 back, once a wave (64^3: 40 us)
     const long long gw = (long long)blockIdx.x * (CL_THREADS / 64) + (threadIdx.x >> 6);
+    auto publish = [&](int i, double v) {
+        const unsigned long long old =
+            __hip_atomic_exchange(reinterpret_cast<unsigned long long *>(a.partials + gw * NF + i),
+                                  (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" ::"v"(old) : "memory");
+    };
     if (col == 0) {
-        a.partials[gw * NF + g] = s0;
-        if (g == 0) a.partials[gw * NF + 4] = s4;
+        publish(g, s0);
+        if (g == 0) publish(4, s4);
     }
-    __threadfence();
     __syncthreads();
-    __shared__ int last;
+    int &last = reinterpret_cast<int *>(wl)[CL_IMAGE - 1];  // the network is no longer read
     if (threadIdx.x == 0) last = atomicAdd(a.done, 1ull) == (unsigned long long)gridDim.x - 1 ? 1 : 0;
     __syncthreads();
     if (!last) return;
-    __threadfence();
-    double *red = reinterpret_cast<double *>(wl);  // the weights are no longer read
+    double *red = reinterpret_cast<double *>(wl);
     const long long nparts = (long long)gridDim.x * (CL_THREADS / 64);
+    double sum[NF] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (long long w = threadIdx.x; w < nparts; w += CL_THREADS)
+#pragma unroll
+        for (int i = 0; i < NF; i++)
+            sum[i] += __hip_atomic_load(a.partials + w * NF + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
     for (int i = 0; i < NF; i++) {
-        double sum = 0.0;
-        for (long long w = threadIdx.x; w < nparts; w += CL_THREADS)
-            sum += __hip_atomic_load(a.partials + w * NF + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        red[threadIdx.x] = sum;
-        __syncthreads();
-        for (int h = CL_THREADS / 2; h > 0; h >>= 1) {
-            if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) a.cmean[i] = red[0] / (double)a.ncells;
-        __syncthreads();
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) sum[i] += __shfl_xor(sum[i], off, 64);
+        if (lane == 0) red[i * (CL_THREADS / 64) + (threadIdx.x >> 6)] = sum[i];
+    }
+    __syncthreads();
+    if (threadIdx.x < NF) {
+        double t = 0.0;
+        for (int w = 0; w < CL_THREADS / 64; w++) t += red[threadIdx.x * (CL_THREADS / 64) + w];
+        a.cmean[threadIdx.x] = t / (double)a.ncells;
     }
     if (threadIdx.x == 0) __hip_atomic_store(a.done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -834,11 +834,7 @@ dg_status run_stage(dg_ctx *c, const void *y0, const void *yin, void *out, doubl
         ClosureArgs ca{};
         ca.y = yin;
         ca.corr = c->corr;
-        ca.params = c->clo;
-        ca.fmean = c->clo + CL_NPARAMS;
-        ca.fistd = ca.fmean + CL_NIN;
-        ca.oscale = ca.fistd + CL_NIN;
-        ca.obound = ca.oscale + CL_NOUT;
+        ca.image = c->clo;
         ca.partials = c->clo_partials + NF;
         ca.fallbacks = c->clo_fallbacks;
         ca.done = c->clo_fallbacks + 1;
@@ -1203,6 +1199,32 @@ dg_status dg_ou_update(int32_t nmodes, const int32_t *nvec, double *theta, const
 
 // ---------------------------------------------------------------- learned closure and its training
 
+// the weights and biases of W1 b1 W2 b2 W3 b3 (W row-major [out][in]) in the inference kernel's order
+static void closure_image(const float *params, float *img) {
+    const float *W1 = params, *b1 = W1 + CL_NH * CL_NIN, *W2 = b1 + CL_NH, *b2 = W2 + CL_NH * CL_NH;
+    const float *W3 = b2 + CL_NH, *b3 = W3 + CL_NOUT * CL_NH;
+    constexpr int S1 = CL_NIN / 4, S2 = CL_NH / 4;
+    for (int st = 0; st < CL_STEPS; st++)
+        for (int j = 0; j < 8; j++)
+            for (int l = 0; l < 64; l++) {
+                const int lr = l & 15, g = l >> 4;
+                float v;
+                if (st < S1) {  // K step st, output tile j
+                    v = W1[(16 * j + lr) * CL_NIN + 4 * st + g];
+                } else if (st < S1 + S2) {  // hidden units 16 t + 4 g + r, output tile j
+                    const int t = (st - S1) / 4, r = (st - S1) % 4;
+                    v = W2[(16 * j + lr) * CL_NH + 16 * t + 4 * g + r];
+                } else {  // the four r of a tile t, two output tiles each; rows past the last output zero
+                    const int t = st - S1 - S2, r = j / 2, row = 16 * (j % 2) + lr;
+                    v = row < CL_NOUT ? W3[row * CL_NH + 16 * t + 4 * g + r] : 0.0f;
+                }
+                img[st * 512 + j / 4 * 256 + l * 4 + j % 4] = v;
+            }
+    std::copy(b1, b1 + CL_NH, img + CL_B1);
+    std::copy(b2, b2 + CL_NH, img + CL_B2);
+    std::copy(b3, b3 + CL_NOUT, img + CL_OUT);
+}
+
 extern "C" {
 
 dg_status dg_set_closure(dg_ctx *c, const float *params, const float *feat_mean, const float *feat_std,
@@ -1216,16 +1238,15 @@ dg_status dg_set_closure(dg_ctx *c, const float *params, const float *feat_mean,
         c->err = "dg_set_closure: NULL pointer";
         return DG_ERR_ARG;
     }
-    std::vector<float> blob((size_t)CL_NPARAMS + 2 * CL_NIN + 2 * CL_NOUT);
-    std::memcpy(blob.data(), params, sizeof(float) * CL_NPARAMS);
-    float *fm = blob.data() + CL_NPARAMS, *fi = fm + CL_NIN, *os = fi + CL_NIN, *ob = os + CL_NOUT;
+    std::vector<float> blob(CL_IMAGE);
+    float *fn = blob.data() + CL_FN, *os = blob.data() + CL_OUT + CL_NOUT, *ob = os + CL_NOUT;
     for (int f = 0; f < CL_NIN; f++) {
         if (!(feat_std[f] > 0.0f) || !std::isfinite(feat_std[f]) || !std::isfinite(feat_mean[f])) {
             c->err = "dg_set_closure: feat_std must be positive and finite, feat_mean finite";
             return DG_ERR_ARG;
         }
-        fm[f] = feat_mean[f];
-        fi[f] = 1.0f / feat_std[f];
+        fn[2 * f] = feat_mean[f];
+        fn[2 * f + 1] = 1.0f / feat_std[f];
     }
     for (int j = 0; j < CL_NOUT; j++) {
         if (!std::isfinite(out_scale[j]) || !(out_bound[j] >= 0.0f)) {
@@ -1235,6 +1256,7 @@ dg_status dg_set_closure(dg_ctx *c, const float *params, const float *feat_mean,
         os[j] = out_scale[j];
         ob[j] = out_bound[j];
     }
+    closure_image(params, blob.data());
     if (!c->clo) {
         const long long nwaves = (c->ncells + 15) / 16;
         if (hipMalloc(&c->clo, blob.size() * sizeof(float)) != hipSuccess ||

@@ -272,14 +272,17 @@ constexpr int CL_NH = 128;
 constexpr int CL_NOUT = CL_ROWS;
 constexpr long long CL_NPARAMS = (long long)CL_NH * CL_NIN + CL_NH + CL_NH * CL_NH + CL_NH + CL_NOUT * CL_NH + CL_NOUT;
 
+// The network as the inference kernel holds it in LDS (floats): per K step of the three layers the eight
+// MFMA A operands of each lane as two blocks [lane][4], 35 + 32 + 8 steps; then (mean, 1 / std) of each
+// feature, the two hidden biases, and bias, scale and bound of the outputs.
+constexpr int CL_STEPS = CL_NIN / 4 + CL_NH / 4 + CL_NH / 16;
+constexpr int CL_FN = CL_STEPS * 512, CL_B1 = CL_FN + 2 * CL_NIN, CL_B2 = CL_B1 + CL_NH, CL_OUT = CL_B2 + CL_NH;
+constexpr int CL_IMAGE = CL_OUT + 3 * CL_NOUT;
+static_assert(CL_IMAGE % 4 == 0, "copied 16 bytes at a time");
 struct ClosureArgs {
     const void *y;
     void *corr;
-    const float *params;   // W1 b1 W2 b2 W3 b3, W row-major [out][in]
-    const float *fmean;    // [CL_NIN]
-    const float *fistd;    // [CL_NIN] 1 / std
-    const float *oscale;   // [CL_NOUT]
-    const float *obound;   // [CL_NOUT]
+    const float *image;    // the network as the kernel holds it in LDS [CL_IMAGE]
     double *partials;      // [waves of the grid][5]
     unsigned long long *fallbacks;
     unsigned long long *done;  // workgroups finished (zero between launches)
@@ -396,7 +399,7 @@ struct dg_ctx {
     int lds = 0;
     long long step_count = 0;
     // closure (DG_CLOSURE)
-    float *clo = nullptr;                 // params, fmean, fistd, oscale, obound
+    float *clo = nullptr;                 // the network, CL_IMAGE floats
     void *corr = nullptr;                 // correction, state layout
     double *clo_partials = nullptr;       // per-wave mean-row sums; then [5] means
     unsigned long long *clo_fallbacks = nullptr;
