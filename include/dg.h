@@ -68,7 +68,7 @@ enum {
 };
 
 typedef struct {
-    int32_t k;          /* polynomial degree 0..4: 0 first-order finite volume, 1..3 the MFMA stage kernel,
+    int32_t k;          /* polynomial degree 0..4: 0 first-order finite volume, 1..3 the stage kernels,
                            4 the quadrature-form kernel (FP64 and FP32 storage only) */
     int32_t n[3];       /* cells per axis, each >= 2 */
     double box[3];      /* box lengths (> 0); cell widths are box[a]/n[a] */
