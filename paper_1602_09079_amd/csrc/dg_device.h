@@ -68,6 +68,25 @@ __device__ inline double sqrt64(double x) {
     return x == 0.0 ? x : g;
 }
 
+// CFL rate of a cell from its means (Sec. 2.4); infinite for a non-physical cell: forces dt -> 0
+__device__ inline double cfl_rate(double rho, double mx, double my, double mz, double E, double gamma, double ihx,
+                                  double ihy, double ihz) {
+    const double inv = 1.0 / rho;
+    const double p = (gamma - 1.0) * (E - 0.5 * (mx * mx + my * my + mz * mz) * inv);
+    const double c = sqrt(gamma * p * inv);
+    const double r = (fabs(mx * inv) + c) * ihx + (fabs(my * inv) + c) * ihy + (fabs(mz * inv) + c) * ihz;
+    return r >= 0.0 ? r : __builtin_inf();
+}
+__device__ inline double wave_max(double v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+    return v;
+}
+// into a rate slot; the bit patterns of non-negative doubles order like their values
+__device__ inline void rate_max(double *slot, double m) {
+    atomicMax(reinterpret_cast<unsigned long long *>(slot), (unsigned long long)__double_as_longlong(m));
+}
+
 // ------------------------------------------------------------------ precision policies
 //
 // S: storage type; C: pointwise arithmetic; Acc: MFMA accumulator.

@@ -207,6 +207,8 @@ struct StageArgs {
     const void *tables;   // device copy of the fragment tables (staged into LDS by each workgroup)
     const double *rate;   // device max CFL rate slot, or nullptr to use dt
     double *tacc;         // device time accumulator, advanced by dt when non-null
+    double *next_rate;    // tiles split by task: CFL rate slot that the result's cells go into, or nullptr
+    double *zero_rate;    // tiles split by task: rate slot to clear, or nullptr
     double dt, a, b;
     double dtfac;         // C / (2k+1)
     double gamma;

@@ -1617,22 +1617,16 @@ hipError_t launch_reset(int k, int prec, void *y, const Leg1D &L, long long nc, 
 
 // ------------------------------------------------------------------ CFL reduction (Sec. 2.4)
 
-__device__ inline double wave_max(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
 // index of mode 0 of field i of a cell in the [z][y][i][l][x] layout
 __device__ inline long long mean_index(long long cell, int i, int N, int nx) {
     const long long r = cell / nx;
     return ((r * NF + i) * N) * nx + (cell - r * nx);
 }
 
-// Each workgroup takes items of one run of 1024 cells of a row (several whole rows if they are short), the next one's means requested while this one's
-// rate is formed (so no division by the row length per cell and two rounds of loads in flight); each
-// thread keeps the largest rate of its cells, the workgroup reduces them (wave shuffles, then LDS), and
-// one atomic max per workgroup goes to the slot.  Atomics on one address serialise, so the grid is at
+// Each workgroup takes items of one run of 1024 cells of a row (several whole rows if they are short),
+// the next one's means requested while this one's rate is formed (so no division by the row length per
+// cell and two rounds of loads in flight); each thread keeps the largest rate of its cells, the
+// workgroup reduces them (wave shuffles, then LDS), and one atomic max per workgroup goes to the slot.  Atomics on one address serialise, so the grid is at
 // most CFL_BLOCKS: 64^3 FP32 6.6 us, 256^3 at k = 0 75 us (2048 workgroups of 256 and a 64-bit division
 // per cell: 14 and 106).
 constexpr int CFL_THREADS = 1024, CFL_BLOCKS = 512;
@@ -1660,14 +1654,8 @@ __global__ __launch_bounds__(CFL_THREADS) void cfl_kernel(const S *__restrict__ 
     if (it < items) load(it, cur);
     for (; it < items; it += gridDim.x) {
         if (it + gridDim.x < items) load(it + gridDim.x, nxt);
-        const double rho = (double)cur[0], mx = (double)cur[1], my = (double)cur[2], mz = (double)cur[3];
-        const double E = (double)cur[4];
-        const double inv = 1.0 / rho;
-        const double p = (gamma - 1.0) * (E - 0.5 * (mx * mx + my * my + mz * mz) * inv);
-        const double c = sqrt(gamma * p * inv);
-        double r = (fabs(mx * inv) + c) * ihx + (fabs(my * inv) + c) * ihy + (fabs(mz * inv) + c) * ihz;
-        if (!(r >= 0.0)) r = __builtin_inf();  // non-physical cell: force dt -> 0
-        rate = fmax(rate, r);
+        rate = fmax(rate, cfl_rate((double)cur[0], (double)cur[1], (double)cur[2], (double)cur[3], (double)cur[4], gamma,
+                                   ihx, ihy, ihz));
 #pragma unroll
         for (int i = 0; i < NF; i++) cur[i] = nxt[i];
     }
@@ -1677,8 +1665,7 @@ __global__ __launch_bounds__(CFL_THREADS) void cfl_kernel(const S *__restrict__ 
     if (threadIdx.x == 0) {
         double m = wmax[0];
         for (int w = 1; w < CFL_THREADS / 64; w++) m = fmax(m, wmax[w]);
-        // the bit patterns of non-negative doubles order like their values
-        atomicMax(reinterpret_cast<unsigned long long *>(rate_slot), (unsigned long long)__double_as_longlong(m));
+        rate_max(rate_slot, m);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0 && zero_slot) *zero_slot = 0.0;
 }

@@ -257,6 +257,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     if (a.rate) dtd = a.dtfac / a.rate[0];
     const C dt = uniform((C)dtd);
     if (a.tacc && blockIdx.x == 0 && threadIdx.x == 0) a.tacc[0] += dtd;
+    if (SPLIT && a.zero_rate && blockIdx.x == 0 && threadIdx.x == 0) a.zero_rate[0] = 0.0;
     const C ih[3] = {uniform((C)a.ih[0]), uniform((C)a.ih[1]), uniform((C)a.ih[2])};
 
     C w[NF][N], R[NF][N], mz[NF][NT];  // weights, operator, flux moments of the face below
@@ -840,6 +841,16 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             for (int i = 0; i < NF; i++)
 #pragma unroll
                 for (int l = 0; l < N; l++) po.put(i * N + l, unx, R[i][l]);
+        }
+        // the next step's CFL rate from the means just stored (the same cells, values and arithmetic as
+        // the reduction that the launch would otherwise be followed by)
+        if constexpr (SPLIT) {
+            if (a.next_rate) {
+                const double r = wave_max(keep ? cfl_rate((double)R[0][0], (double)R[1][0], (double)R[2][0], (double)R[3][0],
+                                                          (double)R[4][0], a.gamma, a.ih[0], a.ih[1], a.ih[2])
+                                               : 0.0);
+                if (lane == 0) rate_max(a.next_rate, r);
+            }
         }
     };
 
