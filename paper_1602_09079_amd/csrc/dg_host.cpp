@@ -508,10 +508,11 @@ static int stage_nbx(const dg_ctx *c) {
 }
 // Whether the one-cell-per-lane kernel splits each tile and plane over several waves by task: where the
 // tiles of a plane are so few that a wave's own chain of dependent instructions is the launch's time
-// (stage at 16^3 split / not, us: k = 1 FP64 8.8 / 14.9, k = 2 FP32 13.5 / 30.4, FP64 19.3 / 47.9; at
-// 32^3 9.5 / 12.5 (k = 1 FP32), 28.7 / 35.8, 41 / 59; at 40^2 x 41 the k = 2 FP32 stage loses, 65 / 56).
-// The two forms round differently, so the rule looks at the plane only: a z slab takes the same one as
-// the whole mesh, and the z chunk length does not enter.
+// (stage at 16^3 split / not, us: k = 1 FP64 8.4 / 14.9, k = 2 FP32 13.7 / 30.4, FP64 19.0 / 47.9; at
+// 32^3 8.5 / 12.5 (k = 1 FP32), 27.1 / 35.8, 40 / 59; at 40^3, 30 tiles, the k = 2 FP32 stage loses,
+// 65 / 54, and at 48^3 all but k = 1 FP32).  The two forms round differently, so the rule looks at the
+// plane only: a z slab takes the same one as the whole mesh, and the z chunk length does not enter.  (A
+// long mesh of small planes pays for that: 32 x 32 x 256 k = 2 FP32 199 us, 64^3 of as many cells 113.)
 static bool stage_split(const dg_ctx *c) {
     return ((c->cfg.n[0] + CELL_TX - 1) / CELL_TX) * (long long)((c->cfg.n[1] + CELL_TY - 1) / CELL_TY) <= 16;
 }
