@@ -49,13 +49,17 @@ struct Dims {
     static constexpr int P = n * n;
 };
 
-// FP64 reciprocal and square root of the pointwise physics: the hardware estimate refined by two
-// Newton steps (and, for the root, two corrections of the result), about half of the instructions of
-// the correctly rounded sequences, which also rescale operands this physics does not meet.
+// FP64 reciprocal and square root of the pointwise physics: the hardware estimate refined by two Newton
+// steps (for the root: Goldschmidt's iteration and two corrections of the result), about half of the
+// instructions of the correctly rounded sequences, which also rescale their operands.  The ends of the
+// range are those of 1 / x and sqrt(x): a reciprocal of zero or past the largest double is infinite,
+// that of an infinity zero, and the root of zero or +infinity its operand.  (The first step's form keeps
+// an infinite estimate infinite; the division's fix-up knows zeros and infinities and sets the sign.)
 __device__ inline double rcp64(double x) {
     double y = __builtin_amdgcn_rcp(x);
+    y *= __builtin_fma(-x, y, 2.0);
     y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return __builtin_amdgcn_div_fixup(y, x, 1.0);
 }
 __device__ inline double sqrt64(double x) {
     const double y = __builtin_amdgcn_rsq(x);
@@ -65,7 +69,7 @@ __device__ inline double sqrt64(double x) {
     h = __builtin_fma(h, r, h);
     g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
     g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
-    return x == 0.0 ? x : g;
+    return __builtin_amdgcn_class(x, 0x260) ? x : g;  // zero of either sign, +infinity
 }
 
 // CFL rate of a cell from its means (Sec. 2.4); infinite for a non-physical cell: forces dt -> 0

@@ -1764,4 +1764,22 @@ hipError_t launch_range_check(int prec, const void *y, int N, int nx, long long 
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ FP64 pointwise functions
+
+__global__ void pointwise64_kernel(const double *__restrict__ x, int n, double *rcp, double *root) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    rcp[i] = rcp64(x[i]);
+    root[i] = sqrt64(x[i]);
+}
+
 }  // namespace dgmi
+
+// Not part of dg.h: 1 / x and sqrt(x) as the FP64 kernels form them, over an array on the device, for
+// the test of their range.
+extern "C" int dgmi_pointwise64(const double *x, int n, double *rcp, double *root, void *stream) {
+    if (!x || !rcp || !root || n < 1) return DG_ERR_ARG;
+    hipLaunchKernelGGL(dgmi::pointwise64_kernel, dim3((n + 255) / 256), dim3(256), 0,
+                       reinterpret_cast<hipStream_t>(stream), x, n, rcp, root);
+    return hipGetLastError() == hipSuccess ? DG_OK : DG_ERR_HIP;
+}

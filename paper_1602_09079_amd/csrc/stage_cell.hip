@@ -342,9 +342,11 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             for (int p = 1; p <= K - q; p++) m[t2<K>(p, q)] = fma_(pb[p], t, m[t2<K>(p, q)]);
         }
     };
+    // (The lambdas that solve faces are inlined by attribute: with the FP64 exact solver they pass the
+    // inliner's limit, and as calls they cost half of the kernel's speed or do not compile.)
     // the face between this lane's cell (trace modes at lp) and the cell above (modes at rp, value
     // stride rs), both in LDS: flux moments, the flux F0 subtracted at the points
-    auto face = [&](const C *lp, const C *rp, auto rs_c, const C F0[NF], C m[NF][NT]) {
+    auto face = [&](const C *lp, const C *rp, auto rs_c, const C F0[NF], C m[NF][NT]) __attribute__((always_inline)) {
         constexpr int RSTR = decltype(rs_c)::value;
 #pragma unroll
         for (int f = 0; f < NF; f++)
@@ -441,7 +443,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     };
     // trace modes of the edge cells and of the tile's own low-edge cells, then the fluxes of the 20
     // low-edge faces and their moments
-    auto edges = [&](int z, auto dx_c, auto dy_c) {
+    auto edges = [&](int z, auto dx_c, auto dy_c) __attribute__((always_inline)) {
         constexpr bool DX = decltype(dx_c)::value, DY = decltype(dy_c)::value;
         constexpr int FC0 = DX ? 0 : CTY, NFC = (DX ? CTY : 0) + (DY ? CTX : 0);  // first and number of low-edge faces
         constexpr int LX = DY ? 2 * CTX : 0;                                     // first lane of the x edges' cells
@@ -557,7 +559,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         lds_order();
     };
     // the +x or +y face of every lane; both of its cells take the moments
-    auto side = [&](auto ax_c) {
+    auto side = [&](auto ax_c) __attribute__((always_inline)) {
         constexpr int AX = decltype(ax_c)::value;
         const int ol = opaque(lane), sx = ol & (CTX - 1), sy = ol / CTX;
         // slots of the cell above, of this one, and of the moments from below
@@ -783,7 +785,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
 
     // the +z face of the plane in w, whose mean flux is F0: flux moments mz relative to F0; the next
     // plane's cells are left in w
-    auto zface = [&](int z, C F0[NF]) {
+    auto zface = [&](int z, C F0[NF]) __attribute__((always_inline)) {
         mean_flux(I2{}, F0);
         {
             C t[NF][NT];
