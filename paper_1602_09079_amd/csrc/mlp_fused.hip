@@ -33,27 +33,43 @@ __host__ __device__ inline int mlp_lds_floats(const MlpArgs &a) {
     return MT * (lds_ld(a.nin) + lds_ld(a.h1) + 2 * lds_ld(a.h2) + lds_ld(a.no));
 }
 
-// acc += W[row][k] X[col][k] over k < K; V: 16-byte reads.  Loads past the row's end take its last
-// values instead and meet zeros in LDS; rows past the last one repeat row 0 and are dropped by the
-// caller.  No load is conditional, so the loads of several steps are in flight together.
+// acc += W[row][k] X[col][k] over k < K; V: 16-byte reads.  Rows past the last one repeat row 0 and are
+// dropped by the caller.  No load of a whole step is conditional, so the loads of several are in flight
+// together.  The last step of a K that is no multiple of 16 is requested first; past the row's end it
+// takes zeros, not weights that would meet zeros in LDS (one of them may be infinite).
 template <bool V>
 __device__ inline f4c rows_product(const float *W, int ldw, int row, int rows, int K, const float *xs, int ldx) {
     const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const float *w = W + (size_t)(row < rows ? row : 0) * ldw;
-    f4c acc = f4c{0, 0, 0, 0};
-#pragma unroll 8
-    for (int s = 0; s < K; s += 16) {
-        const int k = s + 4 * g;
-        f4c av;
+    const float *w = W + (size_t)(row < rows ? row : 0) * ldw + 4 * g;
+    const float *x = xs + col * ldx + 4 * g;
+    const int whole = K & ~15, rest = K - whole - 4 * g;  // rest: this lane's weights in the last step
+    f4c acc = f4c{0, 0, 0, 0}, tail = acc;
+    if (whole < K) {
         if (V) {
-            av = *reinterpret_cast<const f4c *>(w + (k < K ? k : K - 4));  // K is a multiple of 4 here
+            if (rest > 0) tail = *reinterpret_cast<const f4c *>(w + whole);  // K is a multiple of 4 here
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; j++) av[j] = w[k + j < K ? k + j : K - 1];
+            for (int j = 0; j < 4; j++)
+                if (j < rest) tail[j] = w[whole + j];
         }
-        const f4c bv = *reinterpret_cast<const f4c *>(xs + col * ldx + k);
+    }
+#pragma unroll 8
+    for (int s = 0; s < whole; s += 16) {
+        f4c av;
+        if (V) {
+            av = *reinterpret_cast<const f4c *>(w + s);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++) av[j] = w[s + j];
+        }
+        const f4c bv = *reinterpret_cast<const f4c *>(x + s);
 #pragma unroll
         for (int j = 0; j < 4; j++) acc = mfma4(av[j], bv[j], acc);
+    }
+    if (whole < K) {
+        const f4c bv = *reinterpret_cast<const f4c *>(x + whole);
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc = mfma4(tail[j], bv[j], acc);
     }
     return acc;
 }
@@ -66,20 +82,31 @@ __device__ inline f4c bias4(const float *b, int m, int n) {
     return v;
 }
 
-// acc += W[m][row] D[col][m] over m < K: the transposed weights
+// acc += W[m][row] D[col][m] over m < K: the transposed weights (the last step as above)
 __device__ inline f4c cols_product(const float *W, int ldw, int row, int rows, int K, const float *ds, int ldd) {
     const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const float *w = W + (row < rows ? row : 0);
-    f4c acc = f4c{0, 0, 0, 0};
+    const float *w = W + (row < rows ? row : 0) + (size_t)(4 * g) * ldw;
+    const float *d = ds + col * ldd + 4 * g;
+    const int whole = K & ~15, rest = K - whole - 4 * g;
+    f4c acc = f4c{0, 0, 0, 0}, tail = acc;
+    if (whole < K) {
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (j < rest) tail[j] = w[(size_t)(whole + j) * ldw];
+    }
 #pragma unroll 8
-    for (int s = 0; s < K; s += 16) {
-        const int m = s + 4 * g;
+    for (int s = 0; s < whole; s += 16) {
         f4c av;
 #pragma unroll
-        for (int j = 0; j < 4; j++) av[j] = w[(size_t)(m + j < K ? m + j : K - 1) * ldw];
-        const f4c bv = *reinterpret_cast<const f4c *>(ds + col * ldd + m);
+        for (int j = 0; j < 4; j++) av[j] = w[(size_t)(s + j) * ldw];
+        const f4c bv = *reinterpret_cast<const f4c *>(d + s);
 #pragma unroll
         for (int j = 0; j < 4; j++) acc = mfma4(av[j], bv[j], acc);
+    }
+    if (whole < K) {
+        const f4c bv = *reinterpret_cast<const f4c *>(d + whole);
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc = mfma4(tail[j], bv[j], acc);
     }
     return acc;
 }
