@@ -407,8 +407,11 @@ dg_status dg_set_halo(dg_ctx *ctx, const void *lo, const void *hi);
  * that); it exists for that check and for tuning.  DG_ERR_ARG unless 0 <= len <= n[2]. */
 dg_status dg_set_zchunk(dg_ctx *ctx, int32_t len);
 
-/* The slab's place in the whole mesh for the driving field: its first plane
- * is global plane z0 of nz_global (default 0 of n[2]).  Call before
+/* The slab's place in the whole mesh: its first plane is global plane z0 of
+ * nz_global (default 0 of n[2]).  The driving field is that of the whole mesh
+ * there, and the stage takes the form that the whole mesh's takes, so that the
+ * slabs' result is the whole mesh's bit for bit (without this call, k = 1 and 2
+ * in FP64 and FP32 may differ from it by rounding).  Call before
  * dg_set_forcing.  DG_ERR_ARG unless 0 <= z0 and z0 + n[2] <= nz_global. */
 dg_status dg_set_slab(dg_ctx *ctx, int32_t z0, int32_t nz_global);
 

@@ -507,15 +507,23 @@ static int stage_nbx(const dg_ctx *c) {
     return (c->cfg.n[0] + b - 1) / b;
 }
 // Whether the one-cell-per-lane kernel splits each tile and plane over several waves by task: where the
-// tiles of a plane are so few that a wave's own chain of dependent instructions is the launch's time
-// (stage at 16^3 split / not, us: k = 1 FP64 8.4 / 14.9, k = 2 FP32 13.7 / 30.4, FP64 19.0 / 47.9; at
-// 32^3 8.5 / 12.5 (k = 1 FP32), 27.1 / 35.8, 40 / 59; at 40^3, 30 tiles, the k = 2 FP32 stage loses,
-// 65 / 54, and at 48^3 all but k = 1 FP32).  The two forms round differently, so the rule looks at the
-// plane only: a z slab takes the same one as the whole mesh, and the z chunk length does not enter.  (A
-// long mesh of small planes pays for that: 32 x 32 x 256 k = 2 FP32 199 us, 64^3 of as many cells 113;
-// 8 x 64 x 512, where half of the lanes idle besides, 399 against 336 in the matrix form.)
+// whole mesh has so few tiles and planes that a wave's own chain of dependent instructions is the
+// launch's time.  A compute unit holds one split workgroup at k = 2, so their time grows by the 256, and
+// after three rounds the unsplit form has caught up.  Stage, us, split / unsplit, by tiles x planes:
+//            256        512        768        1024       1536       2048
+//   k = 1
+//     FP32   6.9/11.8   9.2/12.9   10.3/13.2  11.6/13.6  15.9/17.5  19.2/18.3
+//     FP64   9.0/16.9   13.0/18.8  18.3/20.0  21.7/21.2  30.0/33.2  38.4/37.0
+//   k = 2
+//     FP32   14.6/32.8  27.4/35.6  39.4/41.0  52.0/45.8  76.9/54.1  101/57.4
+//     FP64   21.2/51.8  40.0/59.6  57.8/64.7  75.4/71.7  110/117    144/127
+// (the same within 5 % for 1, 2, 4, 8 and 16 tiles of 16 to 2048 planes, and for 36 to 576 tiles of 2 to
+// 8 planes).  The two forms round differently, so a z slab takes the whole mesh's, which dg_set_slab has
+// told it; the z chunk length does not enter.
 static bool stage_split(const dg_ctx *c) {
-    return ((c->cfg.n[0] + CELL_TX - 1) / CELL_TX) * (long long)((c->cfg.n[1] + CELL_TY - 1) / CELL_TY) <= 16;
+    const long long tiles =
+        (long long)((c->cfg.n[0] + CELL_TX - 1) / CELL_TX) * ((c->cfg.n[1] + CELL_TY - 1) / CELL_TY);
+    return tiles * (c->slab_nz > 0 ? c->slab_nz : c->cfg.n[2]) <= (c->cfg.k == 1 ? 1536 : 768);
 }
 static int stage_rows(const dg_ctx *c) { return c->cell ? CELL_TY : stage_rows_per_item(c->cfg.precision); }
 
