@@ -921,6 +921,10 @@ dg_status run_stage(dg_ctx *c, const void *y0, const void *yin, void *out, doubl
 // CFL rate into the free slot; it becomes the current one.
 dg_status run_cfl(dg_ctx *c, const void *y) {
     const int nxt = 1 - c->cur_slot;
+    if (c->slot_stale) {
+        HIPCHK(c, launch_zero_u64(reinterpret_cast<unsigned long long *>(c->slots + nxt), c->stream));
+        c->slot_stale = false;
+    }
     HIPCHK(c, launch_cfl(c->cfg.precision, y, c->N, c->cfg.n[0], c->ncells, c->cfg.gamma, c->h, c->slots + nxt,
                          c->slots + c->cur_slot, c->stream));
     c->cur_slot = nxt;
@@ -1039,8 +1043,8 @@ dg_status dg_step(dg_ctx *c, void *y, void *work, double dt, int32_t nsteps, dou
     const bool check = (c->cfg.flags & DG_CHECK_RANGE) != 0;
     // Small meshes: the last stage of a step forms the rate of the next one, a launch less in the chain
     // (ten steps at 16^3, k = 1 FP64: 300 -> 288 us; on large meshes the reduction is 2% of a step or less,
-    // and its values would stay live in kernels that have no registers left).  Not where the state changes between that stage and the
-    // rate (reset, limiter) or the call may end in between (range check).
+    // and its values would stay live in kernels that have no registers left).  Not where the state changes
+    // between that stage and the rate (reset, limiter) or the call may end in between (range check).
     const bool chain = dev_dt && c->cell && stage_split(c) && !(c->cfg.flags & (DG_LIMIT | DG_ISOTHERMAL | DG_CHECK_RANGE));
     bool have_rate = false;  // this step's rate is in its slot, and the other slot holds the last step's
     for (int it = 0; it < nsteps; it++) {
@@ -1054,11 +1058,15 @@ dg_status dg_step(dg_ctx *c, void *y, void *work, double dt, int32_t nsteps, dou
         if ((st = run_stage(c, y, y, w1, 0.0, 1.0, dt, 1, false, false)) != DG_OK) return st;
         if ((st = run_stage(c, y, w1, w2, 0.75, 0.25, dt, 1, false, true, nullptr, have_rate ? other : nullptr)) != DG_OK)
             return st;
+        if (have_rate) c->slot_stale = false;  // that stage cleared it
         have_rate = chain && it + 1 < nsteps;
         if ((st = run_stage(c, y, w2, y, 1.0 / 3.0, 2.0 / 3.0, dt, 1, dev_dt && t_inout, true, have_rate ? other : nullptr)) !=
             DG_OK)
             return st;
-        if (have_rate) c->cur_slot = 1 - c->cur_slot;
+        if (have_rate) {
+            c->cur_slot = 1 - c->cur_slot;
+            c->slot_stale = true;
+        }
         if (c->cfg.flags & DG_ISOTHERMAL) {  // Sec. 3.2: reset after the step, then the limiter
             HIPCHK(c, run_reset(c, y));
             if (lim)

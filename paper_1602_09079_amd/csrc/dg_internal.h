@@ -398,6 +398,7 @@ struct dg_ctx {
     const void *halo_lo = nullptr, *halo_hi = nullptr;
     int slab_z0 = 0, slab_nz = 0;
     int cur_slot = 1;              // slot holding the latest CFL rate
+    bool slot_stale = false;       // the other slot still holds a rate (else it is zero, as the reduction needs it)
     int lds = 0;
     long long step_count = 0;
     // closure (DG_CLOSURE)
