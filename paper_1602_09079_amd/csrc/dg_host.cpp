@@ -1407,10 +1407,10 @@ size_t dg_mlp_nparams(const int32_t shape[4]) {
 
 size_t dg_mlp_workspace_bytes(const int32_t shape[4], int32_t batch) {
     if (!mlp_shape_ok(shape) || batch < 1) return 0;
+    if (mlp_fused_fits(shape)) return mlp_fused_bytes(shape, batch);
     const size_t B = batch;
     // Xb, H1, H2, Y, Tb, dY, D2, D1 (feature-major) and a loss slot
-    const size_t b = sizeof(float) * B * ((size_t)shape[0] + 2 * shape[1] + 2 * shape[2] + 3 * shape[3]) + 64;
-    return mlp_fused_fits(shape) ? std::max(b, mlp_fused_bytes(shape, batch)) : b;
+    return sizeof(float) * B * ((size_t)shape[0] + 2 * shape[1] + 2 * shape[2] + 3 * shape[3]) + 64;
 }
 
 namespace {
