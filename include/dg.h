@@ -346,9 +346,10 @@ size_t dg_spectrum_workspace_bytes(const dg_ctx *ctx, int32_t S);
  *   v_hat_i(n) = sum_X v_i(X) exp(-2 pi i n.X/M),
  * so that sum_s P(s) is the grid mean of |v|^2; E(k) = P(s) box/(2 pi) at
  * k = 2 pi s / box.  The transforms are hipFFT real-to-complex (FP32 for the
- * FP32-storage tiers, FP64 for DG_FP64; the plan is made on the first call and
- * kept); shells are summed in FP64 in a fixed order (bitwise reproducible, and a
- * shell's value does not depend on nbins).  out: HOST double [nbins], 1 <= nbins <= 4096, shells >= nbins are
+ * FP32-storage tiers, FP64 for DG_FP64; the plan and 16 MB of partial sums are
+ * made on the first call and kept with the context); shells are summed in FP64
+ * in a fixed order (bitwise reproducible, and a shell's value does not depend on
+ * nbins).  out: HOST double [nbins], 1 <= nbins <= 4096, shells >= nbins are
  * dropped.  work: DEVICE, dg_spectrum_workspace_bytes(ctx, S).  Synchronises. */
 dg_status dg_velocity_spectrum(dg_ctx *ctx, const void *y, int32_t S, int32_t nbins, double *out, void *work);
 

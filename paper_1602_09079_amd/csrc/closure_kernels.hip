@@ -243,7 +243,11 @@ __global__ __launch_bounds__(CL_THREADS) void closure_kernel(ClosureArgs a) {
     // one partial per wave of the grid; the last workgroup to finish forms the means from them in a
     // fixed order (and resets the counter for the next launch), so no second kernel is launched.  The
     // partials are exchanged where the counter is counted, past the caches, and their old values awaited
-    // before it is: a __threadfence instead writes the whole L2 back, once a wave (64^3: 40 us)
+    // before it is: a __threadfence instead writes the whole L2 back, once a wave (64^3: 40 us).  In the
+    // language's terms all of these are relaxed and nothing orders the counter after the partials; on this
+    // hardware an exchange whose old value has arrived is done at the memory side for every compute unit,
+    // the barrier makes the count wait for every wave's, and the loads below are issued after the count's
+    // return and read past the caches too.
     const long long gw = (long long)blockIdx.x * (CL_THREADS / 64) + (threadIdx.x >> 6);
     auto publish = [&](int i, double v) {
         const unsigned long long old =
