@@ -276,6 +276,7 @@ __global__ __launch_bounds__(64) void shells_kernel(const C *__restrict__ spec, 
         if (ky > M / 2) ky -= M;
         if (kz > M / 2) kz -= M;
         const int c = ky * ky + kz * kz;
+        if (shell_of(c) >= nb) continue;  // no element of this row is wanted: the shell grows with kx
         const c2 *row = reinterpret_cast<const c2 *>(spec) + r * Mh;
         c2 nxt = row[lane < Mh ? lane : 0];  // the next 64 elements are requested before these are summed
         for (int x0 = 0; x0 < Mh; x0 += 64) {
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(64) void shells_kernel(const C *__restrict__ spec, 
             const c2 v = nxt;
             nxt = row[kx + 64 < Mh ? kx + 64 : 0];
             const int s = kx < Mh ? shell_of(kx * kx + c) : nb;
-            // the first lane has the smallest shell: nothing of this row is wanted any more
+            // the first lane has the smallest shell: the rest of this row is not wanted
             if (__builtin_amdgcn_readfirstlane(s) >= nb) break;
             double p = 0.0;
             if (s < nb) {
