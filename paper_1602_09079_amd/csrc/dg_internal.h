@@ -178,7 +178,7 @@ struct SampleArgs {
     int what;             // 0: the five conserved fields; 1..3: velocity component what-1; 4: statistics
     void *out;            // grid (what 0..3): [field][Z][Y][X] with the pitches below
     long long px, py, pf; // row, plane and field pitches of out, in elements
-    int pair;             // the rows of out allow stores of two elements
+    int pair;             // velocity grids: the rows of out allow stores of two elements
     double gamma;
     double lo, hi;        // PDF range of log10(rho); nbins > 0 enables the PDF
     int nbins;

@@ -17,8 +17,8 @@ long long sample_blocks(long long nc) { return (nc + SAMPLE_THREADS - 1) / SAMPL
 __device__ inline float log10_d(float x) { return log10f(x); }
 __device__ inline double log10_d(double x) { return log10(x); }
 
-// S values of a grid row; pair: S is even and every row starts on a boundary of two elements, so they
-// go out two at a time
+// S values of a velocity grid's row; pair: S is even and every row starts on a boundary of two elements,
+// so they go out two at a time
 template <int S, class C>
 __device__ inline void store_row(C *o, const C v[S], int pair) {
     typedef C c2 __attribute__((ext_vector_type(2)));
@@ -38,8 +38,14 @@ __device__ inline void store_row(C *o, const C v[S], int pair) {
 // WHAT: SAMPLE_FIELDS, SAMPLE_VELOCITY (component A.what - 1; reads only its momentum and the density)
 // or SAMPLE_STATS.
 enum { SAMPLE_FIELDS, SAMPLE_VELOCITY, SAMPLE_STATS };
+// Waves per SIMD.  The five fields in FP64 write rows of 24 and 32 bytes a lane, and more waves at it only
+// spread the writes: 64^3 at S = 4, k = 2 180 us with the three waves that fit, 147 with one (4.6 TB/s of
+// output), k = 3 209 and 182; k = 1 151 with eight, 135 with two.
 template <int K, int S, class C, int WHAT>
-__global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(SampleArgs A, Leg1D L) {
+constexpr int sample_waves() { return sizeof(C) == 8 && S >= 3 && WHAT == SAMPLE_FIELDS ? (K >= 2 ? 1 : 2) : 8; }
+template <int K, int S, class C, int WHAT>
+__global__ __launch_bounds__(SAMPLE_THREADS)
+    __attribute__((amdgpu_waves_per_eu(1, sample_waves<K, S, C, WHAT>()))) void sample_kernel(SampleArgs A, Leg1D L) {
     constexpr int N = (K + 1) * (K + 2) * (K + 3) / 6;
     constexpr bool stats = WHAT == SAMPLE_STATS;
     __shared__ double red[stats ? SAMPLE_THREADS : 1];
@@ -112,9 +118,11 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_kernel(SampleArgs A, Le
                     C q[S][S];
                     eval(i, q);
 #pragma unroll
-                    for (int b = 0; b < S; b++)
-                        store_row<S>(o + i * A.pf + Z * A.py + (long long)(iy * S + b) * A.px + (long long)ix * S, q[b],
-                                     A.pair);
+                    for (int b = 0; b < S; b++) {
+                        C *row = o + i * A.pf + Z * A.py + (long long)(iy * S + b) * A.px + (long long)ix * S;
+#pragma unroll
+                        for (int a = 0; a < S; a++) row[a] = q[b][a];
+                    }
                 }
             } else if constexpr (WHAT == SAMPLE_VELOCITY) {
                 C *o = static_cast<C *>(A.out);
@@ -190,7 +198,7 @@ template <int K, int S>
 static hipError_t launch_sample_ks(int prec, SampleArgs a, const Leg1D &L, hipStream_t s) {
     const long long nb = sample_blocks(a.nc);
     const size_t two = prec == DG_FP64 ? 16 : 8;
-    a.pair = a.px % 2 == 0 && a.py % 2 == 0 && a.pf % 2 == 0 && reinterpret_cast<uintptr_t>(a.out) % two == 0;
+    a.pair = a.px % 2 == 0 && a.py % 2 == 0 && reinterpret_cast<uintptr_t>(a.out) % two == 0;
     const bool f64 = prec == DG_FP64;
     const dim3 grid(nb), block(SAMPLE_THREADS);
     if (a.what == 0) {
