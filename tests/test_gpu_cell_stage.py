@@ -1,7 +1,7 @@
-"""The one-cell-per-lane stage kernel (k = 1, 2 in FP64 and FP32) at the edges of its tiles of 8 x 8
-cells, in both of its forms (one wave per tile; tiles split over waves by task where a plane has at
-most 16 tiles), against the FP64 oracle, and the properties its dispatch keeps: the z chunk length and
-a z slab do not change a bit, and planes of 2 GiB and more (64-bit addresses) get the same result.
+"""The one-cell-per-lane stage kernel (k = 1, 2 in FP64 and FP32) on small and ragged meshes (its tiles
+are 16 x 4 cells; these meshes take the form whose tiles are split over waves by task), against the FP64
+oracle, and the properties its dispatch keeps: the z chunk length and a z slab do not change a bit, and
+planes of 2 GiB and more (64-bit addresses) get the same result.
 
 Tolerances on R as for the other stage kernels: ||R_gpu,i - R_orc,i|| / max_j ||R_orc,j|| <= 1e-12
 (FP64), 2e-5 (FP32)."""
@@ -40,8 +40,7 @@ def state(s, n, seed=3):
     return torch.from_numpy(to_abi(y)).to("cuda", s.dtype)
 
 
-# a single tile and one past its end; exact tiles and one cell more, on both sides of 16 tiles per
-# plane; axes of 2 cells
+# fewer cells than a tile along x; exact tiles and ragged ones; axes of 2 cells
 @pytest.mark.parametrize("n", [(8, 8, 2), (9, 7, 3), (32, 32, 2), (40, 32, 3), (33, 33, 2), (2, 130, 2), (131, 2, 3)])
 @pytest.mark.parametrize("k", [1, 2])
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])

@@ -44,7 +44,8 @@ def test_chunks_of_several_planes(dgm, prec, n):
         d = from_abi(r.cpu().numpy()).reshape(5, -1) - want
         err = np.linalg.norm(d, axis=1) / np.linalg.norm(want, axis=1).max()
         assert np.all(err <= 1e-12), err
-    # a slab of it, its other neighbours in halo planes: the same bits
+    # a slab of it, its other neighbours in halo planes: the same to rounding (its box over its planes is
+    # not exactly the whole mesh's cell height)
     part = dgm.Solver(0, (n[0], n[1], 40), box=(1.0, 1.0, 40 / n[2]), gamma=G, precision=prec, zhalo=True)
     part.set_halo(y[6].clone(), y[47].clone())
     got, ref = part.rhs(y[7:47].clone()), r[7:47]
