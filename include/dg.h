@@ -412,7 +412,8 @@ dg_status dg_set_zchunk(dg_ctx *ctx, int32_t len);
  * nz_global (default 0 of n[2]).  The driving field is that of the whole mesh
  * there, and the stage takes the form that the whole mesh's takes, so that the
  * slabs' result is the whole mesh's bit for bit (without this call, k = 1 and 2
- * in FP64 and FP32 may differ from it by rounding).  Call before
+ * in FP64 and FP32 may differ from it by rounding; so do slabs of a column of
+ * n[0] <= 14, n[1] = 2 and more than 256 planes at k = 2 in FP64).  Call before
  * dg_set_forcing.  DG_ERR_ARG unless 0 <= z0 and z0 + n[2] <= nz_global. */
 dg_status dg_set_slab(dg_ctx *ctx, int32_t z0, int32_t nz_global);
 

@@ -613,6 +613,14 @@ dg_status dg_init(const dg_config *cfg, void *hip_stream, dg_ctx **out) {
     c->k3x = cfg->k == 3 && cfg->precision != DG_FP64;
     c->k4m = cfg->k == 4;
     c->cell = (cfg->k == 1 || cfg->k == 2) && (cfg->precision == DG_FP64 || cfg->precision == DG_FP32);
+    // A column of at most one x-block and two rows, k = 2 in FP64: a tile's other two rows idle, and past
+    // one round of split workgroups (256 planes) the matrix form, a wave per row, is the faster one.  Driven
+    // stage, us, matrix / one cell per lane: 14 x 2 x 256 26 / 20,
+    // x 320 26 / 37, x 1024 47 / 69, x 4096 161 / 222; with three rows 2 x 3 x 512 45 / 37, with two
+    // blocks 16 x 2 x 512 46 / 38.  (Slabs of such a mesh keep the one-cell-per-lane kernel.)
+    if (cfg->k == 2 && cfg->precision == DG_FP64 && cfg->n[0] <= BLK_INNER && cfg->n[1] == 2 && cfg->n[2] > 256 &&
+        !(cfg->flags & DG_ZHALO))
+        c->cell = false;
     if (cfg->k >= 1 && !c->cell) {  // the finite-volume and the one-cell-per-lane kernels need no product tables
         std::vector<char> blob;
         if (c->k4m) {

@@ -1,7 +1,7 @@
 // HIP kernels of libdgmi.so for gfx950 (MI355X).
 //
-// The fused SSP stage kernel of this file (k = 3 in FP64, k = 1 and 2 in the BF16-product tiers)
-// evaluates the modal DG operator of Bauer et al.
+// The fused SSP stage kernel of this file (k = 3 in FP64, k = 1 and 2 in the BF16-product tiers, long
+// columns of cells at k = 2 in FP64) evaluates the modal DG operator of Bauer et al.
 // (arXiv 1602.09079), Sec. 2.3, on blocks of 16 cells that are consecutive in
 // x.  Every basis contraction is a dense GEMM over cells on the matrix cores:
 //
@@ -1035,7 +1035,7 @@ static hipError_t set_attr_t(int lds_bytes) {
     switch (k * 10 + prec) {                                                          \
         case 12: return CALL<1, DG_BF16> ARGS; case 13: return CALL<1, DG_BF16X3> ARGS; \
         case 22: return CALL<2, DG_BF16> ARGS; case 23: return CALL<2, DG_BF16X3> ARGS; \
-        case 30: return CALL<3, DG_FP64> ARGS;                                        \
+        case 20: return CALL<2, DG_FP64> ARGS; case 30: return CALL<3, DG_FP64> ARGS;   \
         default: return hipErrorInvalidValue;                                         \
     }
 
