@@ -615,9 +615,9 @@ dg_status dg_init(const dg_config *cfg, void *hip_stream, dg_ctx **out) {
     c->cell = (cfg->k == 1 || cfg->k == 2) && (cfg->precision == DG_FP64 || cfg->precision == DG_FP32);
     // A column of at most one x-block and two rows, k = 2 in FP64: a tile's other two rows idle, and past
     // one round of split workgroups (256 planes) the matrix form, a wave per row, is the faster one.  Driven
-    // stage, us, matrix / one cell per lane: 14 x 2 x 256 26 / 20,
-    // x 320 26 / 37, x 1024 47 / 69, x 4096 161 / 222; with three rows 2 x 3 x 512 45 / 37, with two
-    // blocks 16 x 2 x 512 46 / 38.  (Slabs of such a mesh keep the one-cell-per-lane kernel.)
+    // stage, us, matrix / one cell per lane: 14 x 2 x 256 26 / 20, x 320 26 / 37, x 1024 47 / 69, x 4096
+    // 161 / 222; with three rows 2 x 3 x 512 45 / 37, with two blocks 16 x 2 x 512 46 / 38.  (Slabs of such a
+    // mesh keep the one-cell-per-lane kernel.)
     if (cfg->k == 2 && cfg->precision == DG_FP64 && cfg->n[0] <= BLK_INNER && cfg->n[1] == 2 && cfg->n[2] > 256 &&
         !(cfg->flags & DG_ZHALO))
         c->cell = false;
@@ -748,7 +748,8 @@ dg_status dg_init(const dg_config *cfg, void *hip_stream, dg_ctx **out) {
     // rounds x (length + 1), the longer one on ties
     const long long nbx = stage_nbx(c);
     const int rows = stage_rows(c);
-    const int items_per_wg = c->cell ? CELL_WAVES : rows == 1 ? stage_block_threads(cfg->precision) / 64 : 1;  // one item per wave or per workgroup
+    // one item per wave or per workgroup
+    const int items_per_wg = c->cell ? CELL_WAVES : rows == 1 ? stage_block_threads(cfg->precision) / 64 : 1;
     const long long nyg = (cfg->n[1] + rows - 1) / rows;
     const long long resident = std::max(1LL, (long long)per_cu * ncu * items_per_wg);
     long long zl = 1, best = -1;
@@ -1053,7 +1054,8 @@ dg_status dg_step(dg_ctx *c, void *y, void *work, double dt, int32_t nsteps, dou
     // (ten steps at 16^3, k = 1 FP64: 300 -> 288 us; on large meshes the reduction is 2% of a step or less,
     // and its values would stay live in kernels that have no registers left).  Not where the state changes
     // between that stage and the rate (reset, limiter) or the call may end in between (range check).
-    const bool chain = dev_dt && c->cell && stage_split(c) && !(c->cfg.flags & (DG_LIMIT | DG_ISOTHERMAL | DG_CHECK_RANGE));
+    const bool chain =
+        dev_dt && c->cell && stage_split(c) && !(c->cfg.flags & (DG_LIMIT | DG_ISOTHERMAL | DG_CHECK_RANGE));
     bool have_rate = false;  // this step's rate is in its slot, and the other slot holds the last step's
     for (int it = 0; it < nsteps; it++) {
         dg_status st;
@@ -1199,8 +1201,8 @@ dg_status dg_set_forcing(dg_ctx *c, int32_t nmodes, const int32_t *nvec, const d
     GaussNodes xg{};
     double wg[5];
     gauss_rule(c->n, xg.x, wg);
-    HIPCHK(c, launch_accel_cache(c->cfg.k, c->cfg.precision, c->cell, c->fmodes, nmodes, c->cfg.n[0], c->cfg.n[1], c->cfg.n[2],
-                                 c->ncells, xg, c->slab_z0, c->slab_nz > 0 ? c->slab_nz : c->cfg.n[2], c->acache,
+    HIPCHK(c, launch_accel_cache(c->cfg.k, c->cfg.precision, c->cell, c->fmodes, nmodes, c->cfg.n[0], c->cfg.n[1],
+                                 c->cfg.n[2], c->ncells, xg, c->slab_z0, c->slab_nz > 0 ? c->slab_nz : c->cfg.n[2], c->acache,
                                  c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->nfmodes = nmodes;

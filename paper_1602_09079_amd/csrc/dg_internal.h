@@ -197,8 +197,8 @@ hipError_t launch_fill_zero(unsigned long long *p, long long n, hipStream_t s);
 hipError_t launch_sum_into(const double *p, long long n, double *acc, hipStream_t s);
 hipError_t launch_reset(int k, int prec, void *y, const Leg1D &L, long long nc, int nx, double gm1, double ce,
                         double rho0, double vol, double *partials, double *acc, hipStream_t s);
-hipError_t launch_accel_cache(int k, int prec, bool cell, const double *modes, int nmodes, int nx, int ny, int nz, long long nc,
-                              const GaussNodes &xg, int z0, int nzg, void *out, hipStream_t s);
+hipError_t launch_accel_cache(int k, int prec, bool cell, const double *modes, int nmodes, int nx, int ny, int nz,
+                              long long nc, const GaussNodes &xg, int z0, int nzg, void *out, hipStream_t s);
 
 struct StageArgs {
     const void *yin;

@@ -1257,8 +1257,8 @@ static hipError_t launch_accel_k(int prec, const double *modes, int nmodes, int 
     return hipGetLastError();
 }
 
-hipError_t launch_accel_cache(int k, int prec, bool cell, const double *modes, int nmodes, int nx, int ny, int nz, long long nc,
-                              const GaussNodes &xg, int z0, int nzg, void *out, hipStream_t s) {
+hipError_t launch_accel_cache(int k, int prec, bool cell, const double *modes, int nmodes, int nx, int ny, int nz,
+                              long long nc, const GaussNodes &xg, int z0, int nzg, void *out, hipStream_t s) {
     switch (k) {
         case 0: return launch_accel_k<0>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, cell, out, s);
         case 1: return launch_accel_k<1>(prec, modes, nmodes, nx, ny, nz, nc, xg, z0, nzg, cell, out, s);
@@ -1625,10 +1625,10 @@ __device__ inline long long mean_index(long long cell, int i, int N, int nx) {
 
 // Each workgroup takes items of one run of 1024 cells of a row (several whole rows if they are short),
 // the next one's means requested while this one's rate is formed (so no division by the row length per
-// cell and two rounds of loads in flight); each thread keeps the largest rate of its cells, the
-// workgroup reduces them (wave shuffles, then LDS), and one atomic max per workgroup goes to the slot.  Atomics on one address serialise, so the grid is at
-// most CFL_BLOCKS: 64^3 FP32 6.6 us, 256^3 at k = 0 75 us (2048 workgroups of 256 and a 64-bit division
-// per cell: 14 and 106).
+// cell and two rounds of loads in flight); each thread keeps the largest rate of its cells, the workgroup
+// reduces them (wave shuffles, then LDS), and one atomic max per workgroup goes to the slot.  Atomics on
+// one address serialise, so the grid is at most CFL_BLOCKS: 64^3 FP32 6.5 us, 256^3 at k = 0 73 us (2048
+// workgroups of 256 and a 64-bit division per cell: 14 and 106).
 constexpr int CFL_THREADS = 1024, CFL_BLOCKS = 512;
 
 template <class S>

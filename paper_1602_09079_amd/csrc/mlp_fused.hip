@@ -5,8 +5,8 @@
 // What bounds them: latency.  A 4096-sample gradient at 140-128-128-20 is 0.8 GFLOP, 5 us at the FP32
 // matrix rate.  One product per launch left a weight gradient - 152 result tiles, contraction over the
 // whole batch - to 152 waves of 1024 dependent steps each (93 us a product, eight of them), and one
-// workgroup to the loss (87 us).  Measured for one iteration with Adam: 863 -> 42 us (24 for the tiles, 13.5 for the
-// weight gradients, 6.7 for the shares under the profiler).
+// workgroup to the loss (87 us).  Measured for one iteration with Adam: 863 -> 42 us (24 for the tiles,
+// 13.5 for the weight gradients, 6.5 for the shares under the profiler).
 //
 // Contraction order.  A lane feeds four consecutive K steps from one 16-byte read: in step j lane group
 // g takes index 16 s + 4 g + j, in both operands.

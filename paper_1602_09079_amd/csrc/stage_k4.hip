@@ -48,7 +48,6 @@ struct K4Prec<DG_FP64> : Prec<DG_FP64> {
     __device__ static double sqrt_(double x) { return __builtin_sqrt(x); }
 };
 
-
 namespace {
 
 constexpr int K4_NM = 35, K4_E = NF * K4_NM;
