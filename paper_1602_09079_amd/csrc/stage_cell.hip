@@ -44,8 +44,12 @@
 // a tile edge, which two waves solve, gets the same flux in both.
 //
 // Deviation form: the flux of the cell mean is subtracted from every volume and face flux before the
-// moments are formed.  The subtracted terms cancel exactly, and the sums run over the variation
-// inside the cell.
+// moments are formed.  The subtracted terms are the same numbers everywhere, so they cancel exactly, and the
+// sums run over the variation inside the cell.  Point values are interpolated the same way: the variation
+// first, the cell mean last.  The rounding of R is then that of one rounding per point (48^3, Mach number
+// 0.3, FP32: 5.3e-6 of R at k = 1, 7.5e-6 at k = 2).  With the mean inside mode (0, 0) of a face's trace,
+// every point of the face shares its rounding, and R's error is 7.6e-6 and 15.3e-6, in FP64 likewise; the
+// additions cost 5..10 % of a k = 1 launch in FP32.
 
 #include <type_traits>
 
@@ -135,12 +139,14 @@ template <int K>
 struct CellLds {
     static constexpr int NT = (K + 1) * (K + 2) / 2, NV = NF * NT, P = Dims<K>::P, N = Dims<K>::N;
     static constexpr int X = NV * CX_PLANE;         // exchange planes
-    static constexpr int E = 2 * NV * EF;           // low-edge trace modes [side][value][face]
+    // low-edge trace modes [side][value][face], cell means [side][field][face], the tile's cells' mean
+    // fluxes [field][face]
+    static constexpr int E = (2 * NV + 3 * NF) * EF;
     static constexpr int S = NV * 64;               // this tile's trace modes on the face being solved
-    // during the volume integral: the weights but two (k = 2, to free their registers), and the weights
+    // during the volume integral: the weights but the means (k = 2, to free their registers), and the weights
     // of the 40 cells across the tile's edges on their way in from memory: 32 past the y edges
     // (two lanes a cell, half of the modes each), then 8 past the x edges (eight values a load)
-    static constexpr int STASHED = K >= 2 ? NF * N - 2 : 0, W = STASHED * 64, H = N / 2;
+    static constexpr int STASHED = K >= 2 ? NF * (N - 1) : 0, W = STASHED * 64, H = N / 2;
     static constexpr int RAW = W, RAWN = NF * H * 64 + (NF * N + 7) / 8 * 64;
     static constexpr int ELEMS0 = X + (E > S ? E : S), ELEMS = ELEMS0 > RAW + RAWN ? ELEMS0 : RAW + RAWN;
     static_assert(NF * EF * P <= 64 * NV, "the point fluxes fit the cells' slots");
@@ -176,8 +182,19 @@ __device__ inline double from_lds(const int *d, double) {
     return __longlong_as_double(((long long)d[64] << 32) | (unsigned)d[0]);
 }
 
+// lane's value of v
+__device__ inline float lane_value(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(lane << 2, __float_as_int(v)));
+}
+__device__ inline double lane_value(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(lane << 2, (int)(b & 0xffffffffll));
+    const int hi = __builtin_amdgcn_ds_bpermute(lane << 2, (int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | lo);
+}
+
 template <int K, class C>
-constexpr int cell_waves() { return K == 1 ? (sizeof(C) == 8 ? 1 : 3) : (sizeof(C) == 8 ? 1 : 2); }
+constexpr int cell_waves() { return K == 1 ? (sizeof(C) == 8 ? 2 : 3) : (sizeof(C) == 8 ? 1 : 2); }
 
 // Waves of a workgroup that splits one tile and plane by task (small meshes): the x faces, the y
 // faces, the two z faces, and the volume integral; at k = 2 in FP32 one Gauss plane of it each (in
@@ -272,7 +289,8 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
 #pragma unroll
             for (int l = 0; l < N; l++) w[i][l] = pv.get(i * N + l, unx);
     };
-    // trace modes of this lane's cell on a face (sgn = -1, +1), fields as seen from the face
+    // trace modes of this lane's cell on a face (sgn = -1, +1), fields as seen from the face; mode (0, 0)
+    // without the cell mean
     auto trace = [&](auto ax_c, auto sgn_c, C t[NF][NT]) {
         constexpr int AX = decltype(ax_c)::value, SG = decltype(sgn_c)::value;
 #pragma unroll
@@ -281,27 +299,47 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             for (int p = 0; p <= K; p++)
 #pragma unroll
                 for (int q = 0; q <= K - p; q++) {
-                    C s = w[face_field<AX>(f)][face_mode<K, AX>(0, p, q)];
+                    auto term = [&](int r) { return (C)((SG < 0 && (r & 1)) ? -L::E[r] : L::E[r]); };
+                    const C *const wf = w[face_field<AX>(f)];
+                    const bool dev = p + q == 0;
+                    C s = dev ? term(1) * wf[face_mode<K, AX>(1, 0, 0)] : wf[face_mode<K, AX>(0, p, q)];
 #pragma unroll
-                    for (int r = 1; r <= K - p - q; r++)
-                        s = fma_((C)((SG < 0 && (r & 1)) ? -L::E[r] : L::E[r]),
-                                 w[face_field<AX>(f)][face_mode<K, AX>(r, p, q)], s);
+                    for (int r = dev ? 2 : 1; r <= K - p - q; r++)
+                        s = fma_(term(r), wf[face_mode<K, AX>(r, p, q)], s);
                     t[f][t2<K>(p, q)] = s;
                 }
     };
-    // flux of the cell mean along an axis, fields as seen from the face
-    auto mean_flux = [&](auto ax_c, C F[NF]) {
-        constexpr int AX = decltype(ax_c)::value;
-        C q[NF];
+    // fluxes of a state: xx xy xz yy yz zz of the momentum, x y z of the energy (the mass flux is the momentum)
+    auto fluxes = [&](const C q[NF], C f[9]) __attribute__((always_inline)) {
+        const C inv = PR::rcp(q[0]);
+        const C u = q[1] * inv, v = q[2] * inv, ww = q[3] * inv;
+        const C p = g1 * (q[4] - C(0.5) * (q[1] * u + q[2] * v + q[3] * ww));
+        const C ep = q[4] + p;
+        f[0] = q[1] * u + p;
+        f[1] = q[1] * v;
+        f[2] = q[1] * ww;
+        f[3] = q[2] * v + p;
+        f[4] = q[2] * ww;
+        f[5] = q[3] * ww + p;
+        f[6] = ep * u;
+        f[7] = ep * v;
+        f[8] = ep * ww;
+    };
+    // this lane's cell means
+    auto means = [&](C q[NF]) {
 #pragma unroll
-        for (int f = 0; f < NF; f++) q[f] = w[face_field<AX>(f)][0];
-        const C inv = PR::rcp(q[0]), u = q[1] * inv;
-        const C p = g1 * (q[4] - C(0.5) * ((q[1] * q[1] + q[2] * q[2] + q[3] * q[3]) * inv));
-        F[0] = q[1];
-        F[1] = q[1] * u + p;
-        F[2] = q[2] * u;
-        F[3] = q[3] * u;
-        F[4] = (q[4] + p) * u;
+        for (int i = 0; i < NF; i++) q[i] = w[i][0];
+    };
+    // the flux of the cell means q along an axis, fields as seen from the face: the numbers that the volume
+    // integral subtracts, so that they cancel to the last bit
+    auto mean_flux = [&](auto ax_c, const C q[NF], C F[NF]) {
+        constexpr int AX = decltype(ax_c)::value, TENS[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
+        C f[9];
+        fluxes(q, f);
+        F[0] = q[1 + AX];
+#pragma unroll
+        for (int j = 1; j < 4; j++) F[j] = f[TENS[AX][face_field<AX>(j) - 1]];
+        F[4] = f[6 + AX];
     };
     auto solve = [&](const C qL[NF], const C qR[NF], C F[NF]) {
         if constexpr (RS == 1)
@@ -319,19 +357,21 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             o[q] = s;
         }
     };
-    auto point_of = [&](const C o[n], const C pc[n]) -> C {
+    // a point value: the row's variation first, the cell mean last, so that each point's value is rounded
+    // by itself and the points of a face share no rounding of the mean
+    auto point_of = [&](const C o[n], const C pc[n], C mean) -> C {
         C s = o[0];
 #pragma unroll
-        for (int q = 1; q <= K; q++) s = fma_(pc[q], o[q], s);
-        return s;
+        for (int q = K; q >= 1; q--) s = fma_(pc[q], o[q], s);
+        return s + mean;
     };
     // the same at node c, known at compile time: terms whose coefficient is zero drop out
-    auto point_at = [&](const C o[n], int c) -> C {
+    auto point_at = [&](const C o[n], int c, C mean) -> C {
         C s = o[0];
 #pragma unroll
-        for (int q = 1; q <= K; q++)
+        for (int q = K; q >= 1; q--)  // nodes 0 and 2 share the even part
             if (L::P[q][c] != 0.0) s = fma_((C)L::P[q][c], o[q], s);
-        return s;
+        return s + mean;
     };
     // moments of a face's point fluxes: row b's contribution, from its moments s along the last axis
     auto add_row = [&](C m[NT], const C s[n], C wb, const C pb[n]) {
@@ -345,10 +385,17 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     };
     // (The lambdas that solve faces are inlined by attribute: with the FP64 exact solver they pass the
     // inliner's limit, and as calls they cost half of the kernel's speed or do not compile.)
-    // the face between this lane's cell (trace modes at lp) and the cell above (modes at rp, value
-    // stride rs), both in LDS: flux moments, the flux F0 subtracted at the points
-    auto face = [&](const C *lp, const C *rp, auto rs_c, const C F0[NF], C m[NF][NT]) __attribute__((always_inline)) {
-        constexpr int RSTR = decltype(rs_c)::value;
+    // the face between this lane's cell (trace modes at lp, means lm) and the cell above (modes at rp,
+    // value stride rs, means rm), the modes in LDS: flux moments, the flux F0 subtracted at the points
+    auto face = [&](auto ax_c, const C *lp, const C lm[NF], const C *rp, auto rs_c, const C rm[NF], const C F0[NF],
+                    C m[NF][NT]) __attribute__((always_inline)) {
+        constexpr int AX = decltype(ax_c)::value, RSTR = decltype(rs_c)::value;
+        // One point after the other: the compiler otherwise interpolates a row's points ahead of their solves
+        // and spills about 100 registers at k = 2 (128^3 undriven, us: FP32 894 -> 547, FP64 1611 -> 1259).  At
+        // k = 1 in FP64 it leaves 256 registers, two waves per SIMD (466 -> 387).  k = 1 in FP32 has the
+        // registers (181, 183 with it); in the split form the chain's latency counts (16^3 k = 2 FP32 14.5,
+        // 14.9 with it).
+        constexpr bool PIN = !SPLIT && (K == 2 || sizeof(C) == 8);
 #pragma unroll
         for (int f = 0; f < NF; f++)
 #pragma unroll
@@ -373,8 +420,8 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                 C qL[NF], qR[NF], F[NF];
 #pragma unroll
                 for (int f = 0; f < NF; f++) {
-                    qL[f] = point_at(ol[f], c);
-                    qR[f] = point_at(orr[f], c);
+                    qL[f] = point_at(ol[f], c, lm[face_field<AX>(f)]);
+                    qR[f] = point_at(orr[f], c, rm[face_field<AX>(f)]);
                 }
                 solve(qL, qR, F);
 #pragma unroll
@@ -384,6 +431,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                     for (int q = 0; q <= K; q++)
                         if (L::P[q][c] != 0.0) s[f][q] = fma_((C)(L::W[c] * L::P[q][c]), d, s[f][q]);
                 }
+                if constexpr (PIN) pin(s);
             }
 #pragma unroll
             for (int f = 0; f < NF; f++) add_row(m[f], s[f], wb, pb);
@@ -443,8 +491,10 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         if ((NF * N) % 8 != 0 && el < (NF * N) % 8 * 8) px.to_lds(NF * N / 8 * 8, unx, dst + NF * N / 8 * 64);
     };
     // trace modes of the edge cells and of the tile's own low-edge cells, then the fluxes of the 20
-    // low-edge faces and their moments
-    auto edges = [&](int z, auto dx_c, auto dy_c) __attribute__((always_inline)) {
+    // low-edge faces and their moments, relative to the mean flux of the tile's cell; em: the means of the
+    // edge cell that this lane took (those past the high edges are asked for by the lanes next to them)
+    constexpr int EYH = CTX, EXH = (SPLIT ? 0 : 2 * CTX) + CTY;  // first lane of the y, x high-edge cells
+    auto edges = [&](int z, auto dx_c, auto dy_c, C em[NF]) __attribute__((always_inline)) {
         constexpr bool DX = decltype(dx_c)::value, DY = decltype(dy_c)::value;
         constexpr int FC0 = DX ? 0 : CTY, NFC = (DX ? CTY : 0) + (DY ? CTX : 0);  // first and number of low-edge faces
         constexpr int LX = DY ? 2 * CTX : 0;                                     // first lane of the x edges' cells
@@ -474,7 +524,10 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                     ew[i][l] = from_lds(raw + (ol & 7) + (NF * LD::H + val / 8) * WD + val % 8 * 8, C());
                 }
         }
+#pragma unroll
+        for (int i = 0; i < NF; i++) em[i] = ew[i][0];
         lds_order();
+        C *const lmean = le + 2 * NV * EF;
         if (ol < LX + (DX ? 2 * CTY : 0)) {
             const bool hi = ay ? ol >= CTX : ol >= LX + CTY;
             const int j = ay ? cx : ol & (CTY - 1);
@@ -488,13 +541,15 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             for (int i = 0; i < NF; i++) {
                 const int f = i == 1 ? (ay ? 2 : 1) : i == 2 ? (ay ? 1 : 2) : i;
                 C *dst = lds + d0 + f * NT * stride;
+                if (!hi) lmean[f * EF + (ay ? CTY : 0) + j] = em[i];
 #pragma unroll
                 for (int p = 0; p <= K; p++)
 #pragma unroll
                     for (int q = 0; q <= K - p; q++) {
-                        C s = ew[i][mode_of<K>(0, p, q)];
+                        const bool dev = p + q == 0;
+                        C s = dev ? c1[1] * ew[i][mode_of<K>(1, 0, 0)] : ew[i][mode_of<K>(0, p, q)];
 #pragma unroll
-                        for (int r = 1; r <= K - p - q; r++) s = fma_(c1[r], ew[i][mode_of<K>(r, p, q)], s);
+                        for (int r = dev ? 2 : 1; r <= K - p - q; r++) s = fma_(c1[r], ew[i][mode_of<K>(r, p, q)], s);
                         dst[t2<K>(p, q) * stride] = s;
                     }
             }
@@ -505,6 +560,21 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             if (DX && cx == 0) put_modes(le + opaque(NV * EF + cy), EF, t);
             if constexpr (DY) trace(I1{}, MINUS{}, t);
             if (DY && cy == 0) put_modes(le + opaque(NV * EF + CTY + cx), EF, t);
+#pragma unroll
+            for (int f = 0; f < NF; f++) {
+                if (DX && cx == 0) lmean[(NF + f) * EF + cy] = w[face_field<0>(f)][0];
+                if (DY && cy == 0) lmean[(NF + f) * EF + CTY + cx] = w[face_field<1>(f)][0];
+            }
+            C q[NF], F0[NF];
+            means(q);
+            if constexpr (DX) mean_flux(I0{}, q, F0);
+#pragma unroll
+            for (int f = 0; f < NF; f++)
+                if (DX && cx == 0) lmean[(2 * NF + f) * EF + cy] = F0[f];
+            if constexpr (DY) mean_flux(I1{}, q, F0);
+#pragma unroll
+            for (int f = 0; f < NF; f++)
+                if (DY && cy == 0) lmean[(2 * NF + f) * EF + CTY + cx] = F0[f];
         }
         lds_order();
 #pragma unroll 1
@@ -521,13 +591,13 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             for (int f = 0; f < NF; f++) {
                 C o[n];
                 row_of(le + f * NT * EF + fc, EF, pb, o);
-                qL[f] = point_of(o, pc);
+                qL[f] = point_of(o, pc, lmean[f * EF + fc]);
                 row_of(le + (NV + f * NT) * EF + fc, EF, pb, o);
-                qR[f] = point_of(o, pc);
+                qR[f] = point_of(o, pc, lmean[(NF + f) * EF + fc]);
             }
             solve(qL, qR, F);
 #pragma unroll
-            for (int f = 0; f < NF; f++) lx[flux_slot(f * EF * P + e)] = F[f];
+            for (int f = 0; f < NF; f++) lx[flux_slot(f * EF * P + e)] = F[f] - lmean[(2 * NF + f) * EF + fc];
         }
         lds_order();
 #pragma unroll 1
@@ -560,13 +630,15 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         lds_order();
     };
     // the +x or +y face of every lane; both of its cells take the moments
-    auto side = [&](auto ax_c) __attribute__((always_inline)) {
+    auto side = [&](auto ax_c, const C em[NF]) __attribute__((always_inline)) {
         constexpr int AX = decltype(ax_c)::value;
         const int ol = opaque(lane), sx = ol & (CTX - 1), sy = ol / CTX;
         // slots of the cell above, of this one, and of the moments from below
         const int up = AX == 0 ? (sx == CTX - 1 ? SL_XHI + sy : ol + 1) : (sy == CTY - 1 ? SL_YHI + sx : ol + CTX);
         const int down = AX == 0 ? (sx == 0 ? SL_XLO + sy : ol - 1) : (sy == 0 ? SL_YLO + sx : ol - CTX);
-        C F0[NF], m[NF][NT];
+        const bool last = AX == 0 ? sx == CTX - 1 : sy == CTY - 1, first = AX == 0 ? sx == 0 : sy == 0;
+        constexpr int STEP = AX == 0 ? 1 : CTX;
+        C F0[NF], lm[NF], rm[NF], m[NF][NT];
         {
             C t[NF][NT];
             trace(ax_c, MINUS{}, t);
@@ -575,13 +647,16 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             put_modes(le + opaque(lane), 64, t);
         }
         lds_order();
-        mean_flux(ax_c, F0);
-        face(le + ol, lx + up, std::integral_constant<int, CX_PLANE>{}, F0, m);
+        means(lm);
+#pragma unroll
+        for (int i = 0; i < NF; i++) {
+            const C in = lane_value(lm[i], ol + STEP), out = lane_value(em[i], AX == 0 ? EXH + sy : EYH + sx);
+            rm[i] = last ? out : in;
+        }
+        mean_flux(ax_c, lm, F0);
+        face(ax_c, le + ol, lm, lx + up, std::integral_constant<int, CX_PLANE>{}, rm, F0, m);
         lift(ax_c, PLUS{}, m);
         lds_order();
-        // the moments as absolute fluxes for the cell above
-#pragma unroll
-        for (int f = 0; f < NF; f++) m[f][0] += F0[f];
         put_modes(lx + ol, CX_PLANE, m);
         lds_order();
         const C *src = lx + down;
@@ -589,8 +664,13 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         for (int f = 0; f < NF; f++)
 #pragma unroll
             for (int j = 0; j < NT; j++) m[f][j] = src[(f * NT + j) * CX_PLANE];
+        // from the mean flux of the cell below to this one's (the low-edge faces' moments have it already);
+        // the difference is small where the flux is not, so it is taken before the moment is touched
 #pragma unroll
-        for (int f = 0; f < NF; f++) m[f][0] -= F0[f];
+        for (int f = 0; f < NF; f++) {
+            const C d = lane_value(F0[f], ol - STEP) - F0[f];
+            m[f][0] += first ? C(0) : d;
+        }
         lift(ax_c, MINUS{}, m);
         pin(R);
         lds_order();
@@ -604,22 +684,9 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
         for (int j = 0; j < 9; j++)
 #pragma unroll
             for (int l = 0; l < NL; l++) mu[j][l] = C(0);
-        C fb[9];
-        {
-            const C inv = PR::rcp(w[0][0]);
-            const C u = w[1][0] * inv, v = w[2][0] * inv, ww = w[3][0] * inv;
-            const C p = g1 * (w[4][0] - C(0.5) * (w[1][0] * u + w[2][0] * v + w[3][0] * ww));
-            const C ep = w[4][0] + p;
-            fb[0] = w[1][0] * u + p;
-            fb[1] = w[1][0] * v;
-            fb[2] = w[1][0] * ww;
-            fb[3] = w[2][0] * v + p;
-            fb[4] = w[2][0] * ww;
-            fb[5] = w[3][0] * ww + p;
-            fb[6] = ep * u;
-            fb[7] = ep * v;
-            fb[8] = ep * ww;
-        }
+        C q0[NF], fb[9];
+        means(q0);
+        fluxes(q0, fb);
         // driving acceleration at the points of a column, requested two columns ahead; the cache holds a
         // tile's 64 values of a point together, so a read is two whole cache lines
         C ac[3][3][n];
@@ -642,8 +709,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
 #pragma unroll
             for (int i = 0; i < NF; i++)
 #pragma unroll
-                for (int l = 0; l < N; l++)
-                    if (i * N + l < STASHED) wp[(i * N + l) * 64] = w[i][l];
+                for (int l = 1; l < N; l++) wp[(i * (N - 1) + l - 1) * 64] = w[i][l];
             lds_order();
         }
         const C *const ws = lds + opaque(lane);  // the weights' copies
@@ -656,8 +722,8 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                 for (int v = 0; v <= K; v++)
 #pragma unroll
                     for (int ww = 0; ww <= K - v; ww++) {
-                        auto wt = [&](int l) { return i * N + l < STASHED ? ws[(i * N + l) * 64] : w[i][l]; };
-                        C s = wt(mode_of<K>(0, v, ww));
+                        auto wt = [&](int l) { return STASHED && l ? ws[(i * (N - 1) + l - 1) * 64] : w[i][l]; };
+                        C s = v + ww == 0 ? C(0) : wt(mode_of<K>(0, v, ww));
 #pragma unroll
                         for (int u = 1; u <= K - v - ww; u++)
                             if (L::P[u][qa] != 0.0) s = fma_((C)L::P[u][qa], wt(mode_of<K>(u, v, ww)), s);
@@ -694,24 +760,12 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
                     for (int i = 0; i < NF; i++) {
                         C s = Z[i][0];
 #pragma unroll
-                        for (int ww = 1; ww <= K; ww++)
+                        for (int ww = K; ww >= 1; ww--)
                             if (L::P[ww][qc] != 0.0) s = fma_((C)L::P[ww][qc], Z[i][ww], s);
-                        q[i] = s;
+                        q[i] = s + w[i][0];  // the mean last, as on the faces
                     }
-                    const C inv = PR::rcp(q[0]);
-                    const C u = q[1] * inv, v = q[2] * inv, ww = q[3] * inv;
-                    const C p = g1 * (q[4] - C(0.5) * (q[1] * u + q[2] * v + q[3] * ww));
-                    const C ep = q[4] + p;
                     C f[9];
-                    f[0] = q[1] * u + p;
-                    f[1] = q[1] * v;
-                    f[2] = q[1] * ww;
-                    f[3] = q[2] * v + p;
-                    f[4] = q[2] * ww;
-                    f[5] = q[3] * ww + p;
-                    f[6] = ep * u;
-                    f[7] = ep * v;
-                    f[8] = ep * ww;
+                    fluxes(q, f);
 #pragma unroll
                     for (int j = 0; j < 9; j++) {
                         const C d = f[j] - fb[j];
@@ -759,8 +813,7 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
 #pragma unroll
             for (int i = 0; i < NF; i++)
 #pragma unroll
-                for (int l = 0; l < N; l++)
-                    if (i * N + l < STASHED) w[i][l] = ws[(i * N + l) * 64];
+                for (int l = 1; l < N; l++) w[i][l] = ws[(i * (N - 1) + l - 1) * 64];
         }
         // R_l -= 2/h_a sum over l' of d(l, l') mu_l', l' = l with a lower degree of the other parity along
         // axis a: d = sqrt((2u+1)(2u'+1)); the mass flux's moments are the momentum's modes (mode 0 is the
@@ -787,7 +840,9 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
     // the +z face of the plane in w, whose mean flux is F0: flux moments mz relative to F0; the next
     // plane's cells are left in w
     auto zface = [&](int z, C F0[NF]) __attribute__((always_inline)) {
-        mean_flux(I2{}, F0);
+        C lm[NF], rm[NF];
+        means(lm);
+        mean_flux(I2{}, lm, F0);
         {
             C t[NF][NT];
             trace(I2{}, PLUS{}, t);
@@ -797,7 +852,8 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             put_modes(lx + opaque(lane), 64, t);
         }
         lds_order();
-        face(lds + LD::S + opaque(lane), lx + opaque(lane), std::integral_constant<int, 64>{}, F0, mz);
+        means(rm);
+        face(I2{}, lds + LD::S + opaque(lane), lm, lx + opaque(lane), std::integral_constant<int, 64>{}, rm, F0, mz);
         lds_order();
     };
 
@@ -864,14 +920,15 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
 #pragma unroll
             for (int l = 0; l < N; l++) R[i][l] = C(0);
     };
-    // the flux moments of the face below, absolute with respect to F0, onto this cell's mean flux
+    // the flux moments of the face below, relative to F0, onto this cell's mean flux
     auto rebase = [&]() {
+        C q[NF], F[NF];
+        means(q);
+        mean_flux(I2{}, q, F);
 #pragma unroll
-        for (int f = 0; f < NF; f++) mz[f][0] += F0[f];
-        mean_flux(I2{}, F0);
-#pragma unroll
-        for (int f = 0; f < NF; f++) mz[f][0] -= F0[f];
+        for (int f = 0; f < NF; f++) mz[f][0] += F0[f] - F[f];
     };
+    C em[NF];
     if constexpr (SPLIT) {
         using SP = CellSplit<K, C>;
         if (wave < 2) {
@@ -882,11 +939,11 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             load_cells(z0);
             clear();
             if (wave == 0) {
-                edges(z0, YES{}, NO{});
-                side(I0{});
+                edges(z0, YES{}, NO{}, em);
+                side(I0{}, em);
             } else {
-                edges(z0, NO{}, YES{});
-                side(I1{});
+                edges(z0, NO{}, YES{}, em);
+                side(I1{}, em);
             }
         } else if (wave == 2) {
             load_cells(z0 - 1);
@@ -941,9 +998,9 @@ __device__ __forceinline__ void cell_stage(const StageArgs &a) {
             request_edges(z, YES{}, YES{});
             volume(z, I0{}, std::integral_constant<int, n>{});
             pin(R);
-            edges(z, YES{}, YES{});
-            side(I0{});
-            side(I1{});
+            edges(z, YES{}, YES{}, em);
+            side(I0{}, em);
+            side(I1{}, em);
             zface(z, F0);
             lift(I2{}, PLUS{}, mz);
             finish(z);
