@@ -509,21 +509,22 @@ static int stage_nbx(const dg_ctx *c) {
 // Whether the one-cell-per-lane kernel splits each tile and plane over several waves by task: where the
 // whole mesh has so few tiles and planes that a wave's own chain of dependent instructions is the
 // launch's time.  A compute unit holds one split workgroup at k = 2, so their time grows by the 256, and
-// after three rounds the unsplit form has caught up.  Stage, us, split / unsplit, by tiles x planes:
-//            256        512        768        1024       1536       2048
+// after two rounds in FP32 and three in FP64 the unsplit form has caught up.  Driven stage, us, split /
+// unsplit, by tiles x planes (16 tiles; 640 tells that it is the rounds that count):
+//            256        512        640        768        1024       1536       2048
 //   k = 1
-//     FP32   6.9/11.8   9.2/12.9   10.3/13.2  11.6/13.6  15.9/17.5  19.2/18.3
-//     FP64   9.0/16.9   13.0/18.8  18.3/20.0  21.7/21.2  30.0/33.2  38.4/37.0
+//     FP32   7.5/13.0   9.4/13.8   10.4/14.4  10.5/14.5  12.0/14.8  16.5/18.7  20.2/18.6
+//     FP64   9.6/18.5   13.0/19.8  19.1/21.1  19.3/21.2  23.0/22.2  32.3/31.5  41.0/32.4
 //   k = 2
-//     FP32   14.6/32.8  27.4/35.6  39.4/41.0  52.0/45.8  76.9/54.1  101/57.4
-//     FP64   21.2/51.8  40.0/59.6  57.8/64.7  75.4/71.7  110/117    144/127
-// (the same within 5 % for 1, 2, 4, 8 and 16 tiles of 16 to 2048 planes, and for 36 to 576 tiles of 2 to
-// 8 planes).  The two forms round differently, so a z slab takes the whole mesh's, which dg_set_slab has
-// told it; the z chunk length does not enter.
+//     FP32   15.0/32.3  28.2/34.4  41.1/36.0  41.7/36.5  55.5/37.6  81.7/45.7  108/48.3
+//     FP64   20.8/51.0  40.0/57.5  57.8/59.1  58.9/61.1  77.4/68.1  115/112    153/124
+// (the same within 5 % for one tile and 144 tiles).  The two forms round differently, so a z slab takes the
+// whole mesh's, which dg_set_slab has told it; the z chunk length does not enter.
 static bool stage_split(const dg_ctx *c) {
     const long long tiles =
         (long long)((c->cfg.n[0] + CELL_TX - 1) / CELL_TX) * ((c->cfg.n[1] + CELL_TY - 1) / CELL_TY);
-    return tiles * (c->slab_nz > 0 ? c->slab_nz : c->cfg.n[2]) <= (c->cfg.k == 1 ? 1536 : 768);
+    const int most = c->cfg.k == 1 ? 1536 : c->cfg.precision == DG_FP64 ? 768 : 512;
+    return tiles * (c->slab_nz > 0 ? c->slab_nz : c->cfg.n[2]) <= most;
 }
 static int stage_rows(const dg_ctx *c) { return c->cell ? CELL_TY : stage_rows_per_item(c->cfg.precision); }
 
@@ -615,8 +616,8 @@ dg_status dg_init(const dg_config *cfg, void *hip_stream, dg_ctx **out) {
     c->cell = (cfg->k == 1 || cfg->k == 2) && (cfg->precision == DG_FP64 || cfg->precision == DG_FP32);
     // A column of at most one x-block and two rows, k = 2 in FP64: a tile's other two rows idle, and past
     // one round of split workgroups (256 planes) the matrix form, a wave per row, is the faster one.  Driven
-    // stage, us, matrix / one cell per lane: 14 x 2 x 256 26 / 20, x 320 26 / 37, x 1024 47 / 69, x 4096
-    // 161 / 222; with three rows 2 x 3 x 512 45 / 37, with two blocks 16 x 2 x 512 46 / 38.  (Slabs of such a
+    // stage, us, matrix / one cell per lane: 14 x 2 x 256 26 / 20, x 320 26 / 38, x 1024 47 / 65, x 4096
+    // 162 / 215; with three rows 2 x 3 x 512 45 / 38, with two blocks 16 x 2 x 512 46 / 38.  (Slabs of such a
     // mesh keep the one-cell-per-lane kernel.)
     if (cfg->k == 2 && cfg->precision == DG_FP64 && cfg->n[0] <= BLK_INNER && cfg->n[1] == 2 && cfg->n[2] > 256 &&
         !(cfg->flags & DG_ZHALO))

@@ -1,6 +1,6 @@
 """The one-cell-per-lane stage kernel (k = 1, 2 in FP64 and FP32) on both sides of its form rule: tiles of
-16 x 4 cells times planes of the whole mesh, split over waves by task up to 1536 (k = 1) or 768 (k = 2),
-one wave a tile and chunk beyond.  Meshes just inside and just past the rule, one exact tile and one cell
+16 x 4 cells times planes of the whole mesh, split over waves by task up to 1536 (k = 1) or 768 (k = 2; in
+FP32 512), one wave a tile and chunk beyond.  Meshes just inside and just past the rule, one exact tile and one cell
 more, against the FP64 oracle; the form a z slab takes; the production form of four waves a workgroup;
 and the form's time where the other one takes well over half as long again.
 
@@ -50,6 +50,13 @@ def test_rhs_about_the_form_rule(dgm, prec, k, n):  # noqa: F811
     s, frc = driven(dgm, k, n, prec)
     y = state(s, n)
     check(s, k, n, prec, y, s.rhs(y), frc)
+
+
+@pytest.mark.parametrize("n", [(32, 32, 32), (32, 32, 33), (16, 3, 512), (5, 4, 513)])
+def test_rhs_about_the_line_of_k2_fp32(dgm, n):  # noqa: F811
+    s, frc = driven(dgm, 2, n, "fp32")
+    y = state(s, n)
+    check(s, 2, n, "fp32", y, s.rhs(y), frc)
 
 
 @pytest.mark.parametrize("k,nz", [(1, 90), (2, 45)])
