@@ -8,10 +8,10 @@
 // no row is padding.
 //
 // Measured, one driven stage repeated on the same input, us, matrix form -> this one: 64^3 k = 1 FP32
-// 161 -> 29, FP64 217 -> 65; k = 2 FP32 230 -> 107, FP64 452 -> 251; a 90 x 77 x 51 mesh at k = 2 FP32
-// 701 -> 172 (14-cell blocks by groups of 8 rows leave more of a ragged mesh idle than tiles).  In whole
-// steps, with inputs from memory, the average launch takes 34 (k = 1 FP32), 123 and 277 (k = 2 FP32, FP64)
-// and 194 us (ragged).  k = 2 FP32 at 64^3 issues vector instructions a little over half of the time with
+// 161 -> 31, FP64 217 -> 60; k = 2 FP32 230 -> 88, FP64 452 -> 233; a 90 x 77 x 51 mesh at k = 2 FP32
+// 701 -> 134 (14-cell blocks by groups of 8 rows leave more of a ragged mesh idle than tiles).  In whole
+// steps, with inputs from memory, the average launch takes 36 (k = 1 FP32), 104 and 259 (k = 2 FP32, FP64)
+// and 157 us (ragged).  k = 2 FP32 at 64^3 issues vector instructions about three quarters of the time with
 // two waves per SIMD; the rest is memory and LDS latency.
 //
 // A wave owns a tile of 16 x 4 cells in x and y and sweeps a chunk of z.  Waves are independent:
@@ -26,9 +26,9 @@
 // Meshes of few tiles and planes (cell_split_kernel): with a few waves in flight the time of a launch is
 // one wave's chain of dependent instructions and memory round trips.  There a workgroup takes one tile and
 // one plane and its waves one task each - x faces, y faces, the two z faces, the volume integral - and
-// their shares of R are added through LDS in a fixed order (16^3: k = 1 FP64 15.7 -> 8.4 us, k = 2 FP32
-// 30.3 -> 13.7, FP64 44 -> 19; the waves of the x and the y faces each solve only the tile's low-edge faces
-// of their own axis, 9.8 -> 8.4 us at k = 1 FP64 against all 20 in both).
+// their shares of R are added through LDS in a fixed order (driven 16^3, one wave per tile -> this: k = 1
+// FP64 18.5 -> 9.3 us, k = 2 FP32 32 -> 15, FP64 51 -> 20; the waves of the x and the y faces each solve only
+// the tile's low-edge faces of their own axis, 9.8 -> 8.4 us at k = 1 FP64 against all 20 in both).
 //
 // Volume integral.  The integral of F_a against the gradient of the basis needs the moments of F_a
 // with the polynomials of degree k - 1 only: 1 moment at k = 1, 4 at k = 2, of the 9 distinct
